@@ -35,14 +35,17 @@ struct M3 {
   cx<double> m[9];
 };
 
+// U is component-major: [mu][9][Vphys]
 __device__ inline M3 load_u(const PhysExt2& pe, const double2* __restrict__ U, const int x[4], int mu) {
   bool mir;
-  int64_t s = phys_of(pe, x, mir);
+  const int64_t s = phys_of(pe, x, mir);
+  const double2* u = U + (int64_t)mu * 9 * pe.Vphys + s;
+  const double sg = mir ? -1.0 : 1.0;
   M3 r;
 #pragma unroll
   for (int k = 0; k < 9; ++k) {
-    double2 v = U[(mu * pe.Vphys + s) * 9 + k];
-    r.m[k] = mk(v.x, mir ? -v.y : v.y);
+    const double2 v = u[k * pe.Vphys];
+    r.m[k] = mk(v.x, sg * v.y);
   }
   return r;
 }
@@ -54,6 +57,20 @@ __device__ inline double load_a(const PhysExt2& pe, const double* __restrict__ A
   return mir ? -a : a;
 }
 
+// acc += a b, acc += conj(a) b as fused multiply-adds
+__device__ __forceinline__ void cmac(cx<double>& acc, cx<double> a, cx<double> b) {
+  acc.re = fma(a.re, b.re, acc.re);
+  acc.re = fma(-a.im, b.im, acc.re);
+  acc.im = fma(a.re, b.im, acc.im);
+  acc.im = fma(a.im, b.re, acc.im);
+}
+__device__ __forceinline__ void cmac_conj(cx<double>& acc, cx<double> a, cx<double> b) {
+  acc.re = fma(a.re, b.re, acc.re);
+  acc.re = fma(a.im, b.im, acc.re);
+  acc.im = fma(a.re, b.im, acc.im);
+  acc.im = fma(-a.im, b.re, acc.im);
+}
+
 // a b, a^+ b, a b^+
 __device__ inline M3 mm(const M3& a, const M3& b) {
   M3 r;
@@ -62,8 +79,8 @@ __device__ inline M3 mm(const M3& a, const M3& b) {
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       cx<double> s = a.m[3 * i] * b.m[j];
-      s = s + a.m[3 * i + 1] * b.m[3 + j];
-      s = s + a.m[3 * i + 2] * b.m[6 + j];
+      cmac(s, a.m[3 * i + 1], b.m[3 + j]);
+      cmac(s, a.m[3 * i + 2], b.m[6 + j]);
       r.m[3 * i + j] = s;
     }
   return r;
@@ -75,8 +92,8 @@ __device__ inline M3 mdm(const M3& a, const M3& b) {
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       cx<double> s = cmul_conj(a.m[i], b.m[j]);
-      s = s + cmul_conj(a.m[3 + i], b.m[3 + j]);
-      s = s + cmul_conj(a.m[6 + i], b.m[6 + j]);
+      cmac_conj(s, a.m[3 + i], b.m[3 + j]);
+      cmac_conj(s, a.m[6 + i], b.m[6 + j]);
       r.m[3 * i + j] = s;
     }
   return r;
@@ -88,16 +105,24 @@ __device__ inline M3 mmd(const M3& a, const M3& b) {
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       cx<double> s = cmul_conj(b.m[3 * j], a.m[3 * i]);
-      s = s + cmul_conj(b.m[3 * j + 1], a.m[3 * i + 1]);
-      s = s + cmul_conj(b.m[3 * j + 2], a.m[3 * i + 2]);
+      cmac_conj(s, b.m[3 * j + 1], a.m[3 * i + 1]);
+      cmac_conj(s, b.m[3 * j + 2], a.m[3 * i + 2]);
       r.m[3 * i + j] = s;
     }
   return r;
 }
 
-// E_{mu nu}(x) = csw F + cu1 qhat (i a) 1 for one plane
-__device__ inline M3 plane_tensor(const Geo& g, const PhysExt2& pe, const double2* U, const double* A, const int x[4],
-                                  int mu, int nu, double csw, double cq) {
+// The six planes 01 02 03 12 13 23 and where their tensors stand.
+enum { E01 = 0, E02, E03, E12, E13, E23 };
+
+// E_{mu nu}(x) = csw F + cu1 qhat (i a) 1 for one plane: anti-Hermitian, kept
+// as nine reals, the imaginary diagonal and the entries (0,1), (0,2), (1,2).
+// With W = U_mu(x) (X1 - X4^+) + U_mu(x-mu)^+ (X3 - X2^+), the X's the open
+// staples of the four leaves, Q - Q^+ = W - W^+: ten products and fourteen link
+// loads where the four closed leaves take twelve and sixteen.
+__device__ inline void plane_tensor(const Geo& g, const PhysExt2& pe, const double2* __restrict__ U,
+                                    const double* __restrict__ A, const int x[4], int mu, int nu, double csw,
+                                    double cq, double e[9]) {
   int xpm[4], xpn[4], xmm[4], xmn[4], xmmpn[4], xmmmn[4], xmnpm[4];
   for (int i = 0; i < 4; ++i) xpm[i] = xpn[i] = xmm[i] = xmn[i] = x[i];
   step_coords(g, xpm, mu, +1);
@@ -110,31 +135,6 @@ __device__ inline M3 plane_tensor(const Geo& g, const PhysExt2& pe, const double
   for (int i = 0; i < 4; ++i) xmnpm[i] = xmn[i];
   step_coords(g, xmnpm, mu, +1);
 
-  M3 Q, t;
-  // leaf at corner x: U(x,mu) U(x+mu,nu) U(x+nu,mu)^+ U(x,nu)^+
-  t = mm(load_u(pe, U, x, mu), load_u(pe, U, xpm, nu));
-  t = mmd(t, load_u(pe, U, xpn, mu));
-  Q = mmd(t, load_u(pe, U, x, nu));
-  // leaf at corner x-mu: U(x,nu) U(x-mu+nu,mu)^+ U(x-mu,nu)^+ U(x-mu,mu)
-  t = mmd(load_u(pe, U, x, nu), load_u(pe, U, xmmpn, mu));
-  t = mmd(t, load_u(pe, U, xmm, nu));
-  t = mm(t, load_u(pe, U, xmm, mu));
-  for (int k = 0; k < 9; ++k) Q.m[k] = Q.m[k] + t.m[k];
-  // leaf at corner x-mu-nu: U(x-mu,mu)^+ U(x-mu-nu,nu)^+ U(x-mu-nu,mu) U(x-nu,nu)
-  M3 a = load_u(pe, U, xmm, mu), b = load_u(pe, U, xmmmn, nu);
-  // a^+ b^+ = (b a)^+
-  M3 ba = mm(b, a);
-  for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) t.m[3 * i + j] = conj(ba.m[3 * j + i]);
-  t = mm(t, load_u(pe, U, xmmmn, mu));
-  t = mm(t, load_u(pe, U, xmn, nu));
-  for (int k = 0; k < 9; ++k) Q.m[k] = Q.m[k] + t.m[k];
-  // leaf at corner x-nu: U(x-nu,nu)^+ U(x-nu,mu) U(x-nu+mu,nu) U(x,mu)^+
-  t = mdm(load_u(pe, U, xmn, nu), load_u(pe, U, xmn, mu));
-  t = mm(t, load_u(pe, U, xmnpm, nu));
-  t = mmd(t, load_u(pe, U, x, mu));
-  for (int k = 0; k < 9; ++k) Q.m[k] = Q.m[k] + t.m[k];
-
   // U(1): plaquette angles at the four corners
   auto angle = [&](const int y[4]) {
     int ym[4], yn[4];
@@ -143,66 +143,143 @@ __device__ inline M3 plane_tensor(const Geo& g, const PhysExt2& pe, const double
     step_coords(g, yn, nu, +1);
     return load_a(pe, A, y, mu) + load_a(pe, A, ym, nu) - load_a(pe, A, yn, mu) - load_a(pe, A, y, nu);
   };
-  double a4 = 0.25 * (sin(angle(x)) + sin(angle(xmm)) + sin(angle(xmn)) + sin(angle(xmmmn)));
+  const double a4 = 0.25 * (sin(angle(x)) + sin(angle(xmm)) + sin(angle(xmn)) + sin(angle(xmmmn)));
 
-  M3 E;
-  for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) {
-      cx<double> f = 0.125 * (Q.m[3 * i + j] - conj(Q.m[3 * j + i]));
-      E.m[3 * i + j] = csw * f;
-    }
-  for (int i = 0; i < 3; ++i) E.m[4 * i].im += cq * a4;
-  return E;
+  // X1 = U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+;  X4^+ = U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu)
+  M3 T = mmd(mmd(load_u(pe, U, xpm, nu), load_u(pe, U, xpn, mu)), load_u(pe, U, x, nu));
+  {
+    const M3 t = mdm(load_u(pe, U, xmn, mu), load_u(pe, U, xmn, nu));
+    const M3 s = mdm(load_u(pe, U, xmnpm, nu), t);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) T.m[k] = T.m[k] - s.m[k];
+  }
+  M3 W = mm(load_u(pe, U, x, mu), T);
+  // X3 = U_nu(x-mu-nu)^+ U_mu(x-mu-nu) U_nu(x-nu);  X2^+ = U_nu(x-mu) U_mu(x-mu+nu) U_nu(x)^+
+  T = mm(mdm(load_u(pe, U, xmmmn, nu), load_u(pe, U, xmmmn, mu)), load_u(pe, U, xmn, nu));
+  {
+    const M3 t = mm(load_u(pe, U, xmm, nu), load_u(pe, U, xmmpn, mu));
+    const M3 s = mmd(t, load_u(pe, U, x, nu));
+#pragma unroll
+    for (int k = 0; k < 9; ++k) T.m[k] = T.m[k] - s.m[k];
+  }
+  T = mdm(load_u(pe, U, xmm, mu), T);
+#pragma unroll
+  for (int k = 0; k < 9; ++k) W.m[k] = W.m[k] + T.m[k];
+
+#pragma unroll
+  for (int i = 0; i < 3; ++i) e[i] = csw * (0.125 * (W.m[4 * i].im + W.m[4 * i].im)) + cq * a4;
+  const cx<double> o01 = csw * (0.125 * (W.m[1] - conj(W.m[3]))), o02 = csw * (0.125 * (W.m[2] - conj(W.m[6]))),
+                   o12 = csw * (0.125 * (W.m[5] - conj(W.m[7])));
+  e[3] = o01.re, e[4] = o01.im, e[5] = o02.re, e[6] = o02.im, e[7] = o12.re, e[8] = o12.im;
 }
 
-__global__ __launch_bounds__(128) void k_clover_build(Geo g, PhysExt2 pe, const double2* __restrict__ U,
-                                                      const double* __restrict__ A, double csw, double cq,
-                                                      double diag, double2* __restrict__ He,
-                                                      double2* __restrict__ Ho) {
-  int64_t t = (int64_t)blockIdx.x * 128 + threadIdx.x;
-  if (t >= 2 * (int64_t)g.Ve) return;
-  int p = (int)(t / g.Ve);
-  int h = (int)(t % g.Ve);
+// X = (i/2) (s a + t b) of two anti-Hermitian tensors (entries `stride` apart)
+// at colour (i, j); sc = -1 conjugates both (the mirror half).
+template <int I, int J>
+__device__ __forceinline__ cx<double> half_i(const double* a, const double* b, int stride, double s, double t,
+                                             double sc) {
+  if (I == J) return mk(-0.5 * sc * (s * a[I * stride] + t * b[I * stride]), 0.0);
+  constexpr int lo = I < J ? I : J, hi = I < J ? J : I, k = lo == 0 ? (hi == 1 ? 3 : 5) : 7;
+  const double re = s * a[k * stride] + t * b[k * stride];
+  const double im = sc * (s * a[(k + 1) * stride] + t * b[(k + 1) * stride]);
+  // (i/2)(re + i im); the entry (j, i) is its conjugate
+  return mk(-0.5 * im, (I < J ? 0.5 : -0.5) * re);
+}
+
+// entry (I, J) of the 6 x 6 block of chirality sg: 1/(2 kappa) + sum_l s_l (x) X_l,
+// X_l = (i/2)(sg E_0l - E_Bl), E_B2 = E_31 = -E_13.  E: [6 planes][9][64 sites].
+template <int I, int J>
+__device__ __forceinline__ cx<double> block_entry(const double* E, double sg, double sc, double diag) {
+  constexpr int P = 9 * 64, ai = I % 3, aj = J % 3;
+  if (I / 3 == J / 3) {
+    const cx<double> v = half_i<ai, aj>(E + E03 * P, E + E12 * P, 64, sg, -1.0, sc);
+    const double f = I < 3 ? 1.0 : -1.0;
+    return mk(f * v.re + (I == J ? diag : 0.0), f * v.im);
+  }
+  const cx<double> v1 = half_i<ai, aj>(E + E01 * P, E + E23 * P, 64, sg, -1.0, sc);
+  const cx<double> v2 = half_i<ai, aj>(E + E02 * P, E + E13 * P, 64, sg, 1.0, sc);
+  return v1 - ti(v2);
+}
+
+// the word K of a packed block (0..2: two diagonal entries, 3..17: the entries
+// (0,1), (0,2), .., (4,5))
+template <int K>
+__device__ __forceinline__ double2 block_word(const double* E, double sg, double sc, double diag) {
+  if constexpr (K < 3) {
+    return make_double2(block_entry<2 * K, 2 * K>(E, sg, sc, diag).re,
+                        block_entry<2 * K + 1, 2 * K + 1>(E, sg, sc, diag).re);
+  } else {
+    constexpr int n = K - 3, i = n < 5 ? 0 : n < 9 ? 1 : n < 12 ? 2 : n < 14 ? 3 : 4;
+    constexpr int j = n - (i == 0 ? 0 : i == 1 ? 5 : i == 2 ? 9 : i == 3 ? 12 : 14) + i + 1;
+    const cx<double> v = block_entry<i, j>(E, sg, sc, diag);
+    return make_double2(v.re, v.im);
+  }
+}
+
+template <int K0>
+__device__ __forceinline__ void block_store(const double* E, double sg, double sc, double diag, size_t Ve,
+                                            double2* __restrict__ out) {
+  out[(K0 + 0) * Ve] = block_word<K0 + 0>(E, sg, sc, diag);
+  out[(K0 + 1) * Ve] = block_word<K0 + 1>(E, sg, sc, diag);
+  out[(K0 + 2) * Ve] = block_word<K0 + 2>(E, sg, sc, diag);
+  out[(K0 + 3) * Ve] = block_word<K0 + 3>(E, sg, sc, diag);
+  out[(K0 + 4) * Ve] = block_word<K0 + 4>(E, sg, sc, diag);
+  out[(K0 + 5) * Ve] = block_word<K0 + 5>(E, sg, sc, diag);
+}
+
+constexpr int kClW = 2;  // waves of a workgroup
+// A workgroup takes 64 consecutive physical sites: its waves share the six
+// planes (tensors kept in LDS), then the words of the two blocks, on the site
+// and, with C*, on its mirror image, whose tensors are the complex conjugates:
+// half the products of one work-item per extended site.  One work-item for all
+// six planes of a site needed 9.4 kB of scratch; one plane at a time fits the
+// registers.
+// 64 x 32^3: 36.6 -> 2.04 ms (a wave a plane, six waves: 2.39 ms, one workgroup
+// a CU; two waves of three planes each: two wavefronts a SIMD).  Now bound by
+// the 84 link loads a site (25 GB through the L2) and the FP64 products.
+__global__ __launch_bounds__(64 * kClW, 2) void k_clover_build(Geo g, PhysExt2 pe, const double2* __restrict__ U,
+                                                         const double* __restrict__ A, double csw, double cq,
+                                                         double diag, double2* __restrict__ He,
+                                                         double2* __restrict__ Ho) {
+  __shared__ double E[6 * 9 * 64];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t s = site_tile(blockIdx.x, gridDim.x, 16) * 64 + lane;  // Vphys < 2^31
+  const bool in = s < pe.Vphys;
   int x[4];
-  geo_decode(g, p, h, x[0], x[1], x[2], x[3]);
-  // planes: 01 02 03 12 13 23
-  M3 E01 = plane_tensor(g, pe, U, A, x, 0, 1, csw, cq);
-  M3 E02 = plane_tensor(g, pe, U, A, x, 0, 2, csw, cq);
-  M3 E03 = plane_tensor(g, pe, U, A, x, 0, 3, csw, cq);
-  M3 E12 = plane_tensor(g, pe, U, A, x, 1, 2, csw, cq);
-  M3 E13 = plane_tensor(g, pe, U, A, x, 1, 3, csw, cq);
-  M3 E23 = plane_tensor(g, pe, U, A, x, 2, 3, csw, cq);
-  double2* out = p == 0 ? He : Ho;
-  size_t Ve = g.Ve;
-  for (int b = 0; b < 2; ++b) {
-    double sg = b == 0 ? 1.0 : -1.0;
-    // X_l = (i/2)(sg E_0l - E_Bl);  E_B2 = E_31 = -E_13
-    M3 X1, X2, X3;
-    for (int k = 0; k < 9; ++k) {
-      cx<double> e1 = sg * E01.m[k] - E23.m[k];
-      cx<double> e2 = sg * E02.m[k] + E13.m[k];
-      cx<double> e3 = sg * E03.m[k] - E12.m[k];
-      X1.m[k] = 0.5 * ti(e1);
-      X2.m[k] = 0.5 * ti(e2);
-      X3.m[k] = 0.5 * ti(e3);
-    }
-    double r[36];
-    for (int a = 0; a < 3; ++a) {
-      r[a] = diag + X3.m[4 * a].re;
-      r[3 + a] = diag - X3.m[4 * a].re;
-    }
-    for (int i = 0; i < 6; ++i)
-      for (int j = i + 1; j < 6; ++j) {
-        int si = i / 3, ai = i % 3, sj = j / 3, aj = j % 3;
-        cx<double> v;
-        if (si == 0 && sj == 0) v = X3.m[3 * ai + aj];
-        else if (si == 1 && sj == 1) v = -X3.m[3 * ai + aj];
-        else v = X1.m[3 * ai + aj] - ti(X2.m[3 * ai + aj]);
-        int o = herm6_off(i, j);
-        r[o] = v.re;
-        r[o + 1] = v.im;
+  {
+    uint32_t r = in ? s : (uint32_t)pe.Vphys - 1;  // work-items past the end repeat the last site and store nothing
+    x[3] = r % (uint32_t)pe.L[3];
+    r /= (uint32_t)pe.L[3];
+    x[2] = r % (uint32_t)pe.L[2];
+    r /= (uint32_t)pe.L[2];
+    x[1] = r % (uint32_t)pe.L[1];
+    x[0] = r / (uint32_t)pe.L[1];
+  }
+#pragma unroll 1
+  for (int pl = w; pl < 6; pl += kClW) {
+    const int mu = pl < 3 ? 0 : pl < 5 ? 1 : 2, nu = pl < 3 ? pl + 1 : pl < 5 ? pl - 1 : 3;
+    double e[9];
+    plane_tensor(g, pe, U, A, x, mu, nu, csw, cq, e);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) E[(pl * 9 + k) * 64 + lane] = e[k];
+  }
+  __syncthreads();
+  if (!in) return;
+  const size_t Ve = g.Ve;
+#pragma unroll 1
+  for (int part = w; part < 6; part += kClW) {  // chirality part / 3, words 6 (part % 3) ..
+    const double sg = part < 3 ? 1.0 : -1.0;
+    double2* H = (((x[0] + x[1] + x[2] + x[3]) & 1) ? Ho : He) + (size_t)(part < 3 ? 0 : 18) * Ve;
+    for (int m = 0; m < (g.cstar >= 1 ? 2 : 1); ++m) {
+      double2* out = H + geo_half(g, x[0], x[1] + m * pe.L[1], x[2], x[3]);
+      const double sc = m ? -1.0 : 1.0;
+      switch (part % 3) {
+        case 0: block_store<0>(E + lane, sg, sc, diag, Ve, out); break;
+        case 1: block_store<6>(E + lane, sg, sc, diag, Ve, out); break;
+        default: block_store<12>(E + lane, sg, sc, diag, Ve, out); break;
       }
-    for (int k = 0; k < 18; ++k) out[(18 * b + k) * Ve + h] = make_double2(r[2 * k], r[2 * k + 1]);
+    }
   }
 }
 
@@ -391,7 +468,7 @@ extern "C" qxd_status qxd_clover_build(qxd_handle* h, void* stream) {
   pe.Vphys = h->Vphys;
   double cq = h->fl.u1csw * (double)h->fl.qhat;
   double diag = 1.0 / (2.0 * h->fl.kappa);
-  hipLaunchKernelGGL(k_clover_build, dim3(div_up(2 * h->Ve, 128)), dim3(128), 0, s, h->geo, pe,
+  hipLaunchKernelGGL(k_clover_build, dim3(div_up(h->Vphys, 64)), dim3(64 * kClW), 0, s, h->geo, pe,
                      reinterpret_cast<const double2*>(h->Uphys), h->Aphys, h->fl.su3csw, cq, diag, h->He64,
                      h->Ho64);
   QXD_HIP(hipGetLastError());

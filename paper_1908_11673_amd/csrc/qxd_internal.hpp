@@ -365,8 +365,8 @@ struct qxd_handle {
   qxd_geom g{};
   Geo geo{};
   int64_t V = 0, Ve = 0, Vphys = 0;
-  // gauge field on the physical lattice (canonical layout)
-  double* Uphys = nullptr;  // [4][Vphys][9] complex
+  // gauge field on the physical lattice (canonical site order)
+  double* Uphys = nullptr;  // [4][9][Vphys] complex
   double* Aphys = nullptr;  // [4][Vphys]
   bool has_gauge = false, has_flavour = false, has_clover = false, has_inverse = false;
   qxd_flavour fl{};
