@@ -197,13 +197,19 @@ static qxd_status ensure_t(qxd_handle* h, qxd_prec p) {
 // pass 2 after the last chunk covers the remaining C + 2 slices in one launch.
 // Every site is computed exactly as in the two-launch order (bit-identical
 // results, partial sums indexed by tile), and pass 2 reads t_o and psi_e while
-// they are still in the 256 MB last-level cache.  C is the largest divisor of the time
-// extent (at most half of it) for which the t_o and psi_e of a chunk take at
-// most 256 MB, used when it is at least 8 slices; otherwise (and where the
-// slices are not whole tiles) two plain launches.  Measured at 64x64x32x32
-// (128 tiles a slice): FP64 D_hat 1.786 ms in two launches, 1.688 ms with chunks
-// of 16 slices (8 launches), 1.737 with 8; FP32 0.899 -> 0.862 (32 slices);
-// bf16 storage 0.564 -> 0.556 (32 slices).  At 128x128x64x64 a slice holds
+// they are still in the 256 MB last-level cache.  Lattices whose t_o and psi_e
+// fit that cache as a whole take two plain launches: the chunks then only cost
+// launches and leave each of them a ragged last round of workgroups (32 x 16^3:
+// FP64 138 -> 116 us without them, FP32 73 -> 60, bf16 storage 52 -> 38; 48 x
+// 24^3: 592 -> 575, 293 -> 279, 182 -> 172; 16 x 8^3: 68 -> 35, 40 -> 20, 37 ->
+// 18).  Beyond, C is the largest divisor of the time extent (at most half of
+// it) for which the t_o and psi_e of a chunk take at most 256 MB, used when it
+// is at least 8 slices; otherwise (and where the slices are not whole tiles) two
+// plain launches.  Measured at 64x64x32x32 (128 tiles a slice): FP64 D_hat
+// 1.786 ms in two launches, 1.688 ms with chunks of 16 slices (8 launches),
+// 1.737 with 8; FP32 0.899 -> 0.862 (32 slices); bf16 storage (which fits)
+// 0.538 against 0.536.  At 80x32x32x32 FP64 1.081 -> 1.067, FP32 (which just
+// fits) 0.521 against 0.533 with chunks.  At 128x128x64x64 a slice holds
 // 100 MB per array and chunks of 2, 4 or 8 slices are slower (FP64 27.6 ms ->
 // 29.1-30.0).  Running pass 2 of a chunk on a side stream beside pass 1 of the
 // next was slower as well (1.772 ms).
@@ -213,6 +219,7 @@ static int schur_slices(const qxd_handle* h, qxd_prec p) {
   int c = h->slices_env;
   if (c < 0) {
     const double per_slice = (double)S * 2 * (p == QXD_F64 ? 192 : p == QXD_F32 ? 96 : 48);
+    if (per_slice * h->geo.Le0 <= 256e6) return 0;
     c = (int)(256e6 / per_slice);
   }
   if (c > h->geo.Le0 / 2) c = h->geo.Le0 / 2;
