@@ -13,6 +13,7 @@
 // coordinates (no neighbour table), including the C* shift of x1 when a hop in
 // direction k <= cstar crosses the lattice boundary.
 #include <mutex>
+#include <type_traits>
 
 #include "wilson_site.hpp"
 
@@ -46,13 +47,13 @@ __device__ __forceinline__ double sp_norm2(const cx<T> s[12]) {
 // -> 0.565 ms (in both passes), the FP64 and FP32 passes unchanged.
 
 // pass 1: t_o = H_o^-1 hop_oe(g5? psi_e)
-template <class T, class SPT, class LKT, class CLT, bool DAG>
-__global__ __launch_bounds__(QXD_BLOCK) void k_schur1(Geo g, const SPT* __restrict__ in_e, SPT* __restrict__ t_o,
+template <int BS, class T, class SPT, class LKT, class CLT, bool DAG>
+__global__ __launch_bounds__(BS) void k_schur1(Geo g, const SPT* __restrict__ in_e, SPT* __restrict__ t_o,
                                                       const LKT* __restrict__ Ve_l, const LKT* __restrict__ Vo_l,
                                                       const CLT* __restrict__ Hi) {
   int tile = site_tile(blockIdx.x, gridDim.x, g.tchunk) + g.tile0;
   if (g.ntile && tile >= g.ntile) tile -= g.ntile;
-  int h = tile * QXD_BLOCK + threadIdx.x;
+  int h = tile * BS + threadIdx.x;
   if (h >= g.Ve) return;
   cx<T> acc[12], out[12];
   hop_site<DAG, T>(g, 1, h, in_e, Vo_l, Ve_l, acc);
@@ -62,15 +63,15 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_schur1(Geo g, const SPT* __restri
 }
 
 // pass 2: out_e = H_e psi_e - (1/4) g5? hop_eo(t_o); optional block partials of |out|^2
-template <class T, class SPT, class LKT, class CLT, bool DAG, bool NORM>
-__global__ __launch_bounds__(QXD_BLOCK) void k_schur2(Geo g, const SPT* __restrict__ t_o,
+template <int BS, class T, class SPT, class LKT, class CLT, bool DAG, bool NORM>
+__global__ __launch_bounds__(BS) void k_schur2(Geo g, const SPT* __restrict__ t_o,
                                                       const SPT* __restrict__ in_e, SPT* __restrict__ out_e,
                                                       const LKT* __restrict__ Ve_l, const LKT* __restrict__ Vo_l,
                                                       const CLT* __restrict__ He, double* __restrict__ partial) {
-  __shared__ double sh[QXD_BLOCK / 64];
+  __shared__ double sh[BS / 64];
   int tile = site_tile(blockIdx.x, gridDim.x, g.tchunk) + g.tile0;
   if (g.ntile && tile >= g.ntile) tile -= g.ntile;
-  int h = tile * QXD_BLOCK + threadIdx.x;
+  int h = tile * BS + threadIdx.x;
   double n2 = 0.0;
   if (h < g.Ve) {
     cx<T> acc[12], s[12], c[12];
@@ -90,21 +91,22 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_schur2(Geo g, const SPT* __restri
   }
 }
 
-// full operator on parity p: out_p = H_p in_p - (1/2) hop(in_q)
-template <class T, class SPT, class LKT, class CLT>
-__global__ __launch_bounds__(QXD_BLOCK) void k_dw(Geo g, int p, const SPT* __restrict__ in_p,
-                                                  const SPT* __restrict__ in_q, SPT* __restrict__ out_p,
-                                                  const LKT* __restrict__ Vp, const LKT* __restrict__ Vq,
-                                                  const CLT* __restrict__ Hp) {
-  int h = site_tile(blockIdx.x, gridDim.x, g.tchunk) * QXD_BLOCK + threadIdx.x;
+// full operator on both parities (blockIdx.y), fields and arrays of which lie sp
+// and lk words apart: out_p = H_p in_p - (1/2) hop(in_q)
+template <int BS, class T, class SPT, class LKT, class CLT>
+__global__ __launch_bounds__(BS) void k_dw(Geo g, const SPT* __restrict__ in, SPT* __restrict__ out,
+                                           const LKT* __restrict__ V, const CLT* __restrict__ He,
+                                           const CLT* __restrict__ Ho, size_t sp, size_t lk) {
+  int h = site_tile(blockIdx.x, gridDim.x, g.tchunk) * BS + threadIdx.x;
   if (h >= g.Ve) return;
+  const int p = blockIdx.y;
   cx<T> acc[12], s[12], c[12];
-  hop_site<false, T>(g, p, h, in_q, Vp, Vq, acc);
-  sp_load(in_p, g.Ve, h, s);
-  clover_mul<T>(Hp, g.Ve, h, s, c);
+  hop_site<false, T>(g, p, h, in + (p ? 0 : sp), V + (p ? lk : 0), V + (p ? 0 : lk), acc);
+  sp_load(in + (p ? sp : 0), g.Ve, h, s);
+  clover_mul<T>(p ? Ho : He, g.Ve, h, s, c);
 #pragma unroll
   for (int k = 0; k < 12; ++k) c[k] = c[k] - T(0.5) * acc[k];
-  sp_store(out_p, g.Ve, h, c);
+  sp_store_nt(out + (p ? sp : 0), g.Ve, h, c);
 }
 
 // out_p = C? (base_p + alpha hop(in_q))   (FP64; source preparation and reconstruction)
@@ -125,6 +127,150 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_hop_add(Geo g, int p, const doubl
     sp_store(out, g.Ve, h, c);
   } else {
     sp_store(out, g.Ve, h, s);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The operator with a site's four directions on four wavefronts, for lattices
+// that leave most of the chip idle with one work-item per site.  A workgroup
+// takes 64 sites: wave mu sums both hops along mu, the four sums meet in LDS,
+// and each wave finishes three of a site's twelve components (rows 3 R .. of
+// the block of chirality B).  Such lattices are bound by the serial loads of a
+// wave (FP64: 216 of 16 bytes a lane and pass, 62 here), not by bandwidth:
+// D_hat on 512 even sites 20.0 -> 11.1 us (FP64), 15.9 -> 11.0 (FP32), on 8192
+// 34.6 -> 14.8 and 20.5 -> 11.6, on 32,768 41.8 -> 31.2 and 23.3 -> 19.2.
+
+template <class T>
+struct HopSums {
+  cx<T> v[4][12][64];
+};
+
+// components 6 B .. 6 B + 5 of site h
+template <int B, class T, class SPT>
+__device__ __forceinline__ void sp_load_half(const SPT* __restrict__ f, size_t Ve, int h, cx<T> s[6]) {
+  cx<T> a[12];
+  sp_load(f, Ve, h, a);  // the loads of the other half are dropped where they share no word
+#pragma unroll
+  for (int c = 0; c < 6; ++c) s[c] = a[6 * B + c];
+}
+
+__device__ __forceinline__ void sp_store_one(double2* __restrict__ f, size_t Ve, int h, int c, cx<double> v) {
+  f[c * Ve + h] = make_double2(v.re, v.im);
+}
+__device__ __forceinline__ void sp_store_one(float4* __restrict__ f, size_t Ve, int h, int c, cx<float> v) {
+  reinterpret_cast<float2*>(f + (c >> 1) * Ve + h)[c & 1] = make_float2(v.re, v.im);
+}
+__device__ __forceinline__ void sp_store_one(uint4* __restrict__ f, size_t Ve, int h, int c, cx<float> v) {
+  reinterpret_cast<uint32_t*>(f + (c >> 2) * Ve + h)[c & 3] = pack_bf16x2(v.re, v.im);
+}
+
+// row I of a packed block times v
+template <int I, class T>
+__device__ __forceinline__ cx<T> herm6_row(const T* b, const cx<T> v[6]) {
+  cx<T> o = b[I] * v[I];
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    if (j == I) continue;
+    const int k = j > I ? herm6_off(I, j) : herm6_off(j, I);
+    const cx<T> hij = mk(b[k], b[k + 1]);
+    o = o + (j > I ? hij * v[j] : cmul_conj(hij, v[j]));
+  }
+  return o;
+}
+
+// packed block of chirality B (36 reals)
+template <int B>
+__device__ __forceinline__ void cl_load_half(const double2* __restrict__ C, size_t Ve, int h, double r[36]) {
+#pragma unroll
+  for (int k = 0; k < 18; ++k) {
+    const double2 v = ld_stream(&C[(18 * B + k) * Ve + h]);
+    r[2 * k] = v.x;
+    r[2 * k + 1] = v.y;
+  }
+}
+template <int B>
+__device__ __forceinline__ void cl_load_half(const float4* __restrict__ C, size_t Ve, int h, float r[36]) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const float4 v = ld_stream(&C[(9 * B + k) * Ve + h]);
+    r[4 * k] = v.x;
+    r[4 * k + 1] = v.y;
+    r[4 * k + 2] = v.z;
+    r[4 * k + 3] = v.w;
+  }
+}
+
+// rows 3 R .. 3 R + 2 of chirality B of one site: C g5?(hop), or with BASE
+// C base + alpha g5?(hop); returns their |.|^2
+template <bool BASE, int B, int R, bool G5HOP, class T, class SPT, class CLT>
+__device__ __forceinline__ double hop4_finish(const Geo& g, int h, bool in, HopSums<T>& L,
+                                              const SPT* __restrict__ base, SPT* __restrict__ out,
+                                              const CLT* __restrict__ C, T alpha) {
+  const int lane = threadIdx.x & 63;
+  const size_t Ve = g.Ve;
+  T r[36];
+  cx<T> s[6], a[6];
+  // issued before the barrier: they do not wait for the hops
+  cl_load_half<B>(C, Ve, h, r);
+  if (BASE) sp_load_half<B, T>(base, Ve, h, s);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    a[c] = (L.v[0][6 * B + c][lane] + L.v[1][6 * B + c][lane]) + (L.v[2][6 * B + c][lane] + L.v[3][6 * B + c][lane]);
+    if (G5HOP && B == 1) a[c] = -a[c];
+  }
+  const cx<T>* v = BASE ? s : a;
+  cx<T> o[3] = {herm6_row<3 * R>(r, v), herm6_row<3 * R + 1>(r, v), herm6_row<3 * R + 2>(r, v)};
+  double n2 = 0.0;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    if (BASE) o[c] = o[c] + alpha * a[3 * R + c];
+    if (in) {
+      sp_store_one(out, Ve, h, 6 * B + 3 * R + c, o[c]);
+      n2 += (double)norm2(o[c]);
+    }
+  }
+  return n2;
+}
+
+// out_p = C g5?(hop(g5? in_q)) or (BASE) C base + alpha g5?(hop(g5? in_q)), p the
+// parity of the output; optional workgroup partials of |out|^2.  G5IN: gamma5 on
+// the field the hops read; G5HOP: gamma5 on their sum.
+template <bool BASE, bool G5IN, bool G5HOP, bool NORM, class T, class SPT, class LKT, class CLT>
+__global__ __launch_bounds__(256) void k_hop4(Geo g, int p, const SPT* __restrict__ in_q,
+                                              const SPT* __restrict__ base, SPT* __restrict__ out,
+                                              const LKT* __restrict__ Vp, const LKT* __restrict__ Vq,
+                                              const CLT* __restrict__ C, T alpha, double* __restrict__ partial) {
+  __shared__ HopSums<T> L;
+  __shared__ double sh[4];
+  int tile = site_tile(blockIdx.x, gridDim.x, g.tchunk) + g.tile0;
+  if (g.ntile && tile >= g.ntile) tile -= g.ntile;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool in = tile * 64 + lane < g.Ve;
+  const int h = in ? tile * 64 + lane : g.Ve - 1;  // work-items past the end repeat the last site and store nothing
+  int x0, x1, x2, x3;
+  geo_decode(g, p, h, x0, x1, x2, x3);
+  cx<T> acc[12];
+#pragma unroll
+  for (int c = 0; c < 12; ++c) acc[c] = mk(T(0), T(0));
+  switch (w) {
+    case 0: hop_mu<0, G5IN, T>(g, h, x0, x1, x2, x3, in_q, Vp, Vq, acc); break;
+    case 1: hop_mu<1, G5IN, T>(g, h, x0, x1, x2, x3, in_q, Vp, Vq, acc); break;
+    case 2: hop_mu<2, G5IN, T>(g, h, x0, x1, x2, x3, in_q, Vp, Vq, acc); break;
+    default: hop_mu<3, G5IN, T>(g, h, x0, x1, x2, x3, in_q, Vp, Vq, acc); break;
+  }
+#pragma unroll
+  for (int c = 0; c < 12; ++c) L.v[w][c][lane] = acc[c];
+  double n2;
+  switch (w) {
+    case 0: n2 = hop4_finish<BASE, 0, 0, G5HOP>(g, h, in, L, base, out, C, alpha); break;
+    case 1: n2 = hop4_finish<BASE, 0, 1, G5HOP>(g, h, in, L, base, out, C, alpha); break;
+    case 2: n2 = hop4_finish<BASE, 1, 0, G5HOP>(g, h, in, L, base, out, C, alpha); break;
+    default: n2 = hop4_finish<BASE, 1, 1, G5HOP>(g, h, in, L, base, out, C, alpha); break;
+  }
+  if (NORM) {
+    const double b = block_sum(n2, sh);
+    if (threadIdx.x == 0) partial[tile] = b;
   }
 }
 
@@ -228,46 +374,74 @@ static int schur_slices(const qxd_handle* h, qxd_prec p) {
   return c >= 2 ? c : 0;
 }
 
+// Sites of a workgroup, by the half volume and the spinor precision p.
+//   0: four waves for 64 sites (k_hop4), up to two such workgroups a CU (four
+//      with bf16 storage).  Beyond, one work-item per site fills the chip and its
+//      longer run of loads costs less than the exchange: 41,472 even sites FP64
+//      42.7 us against 44.2, FP32 24.0 against 25.2, 65,536 bf16 24.3 against
+//      22.1, 131,072 bf16 38.4 against 44.9;
+//  64: one wave, so that the last round of workgroups leaves single SIMDs idle
+//      and not CUs: 209,952 FP64 204 -> 197 us, FP32 101.4 -> 97.5;
+// 256: from 2^18 on, where the waves of a workgroup share neighbours in the
+//      L1 (913,952 FP64 773 us against 800 with 64, 2,097,152 1.67 against
+//      1.75 ms) and the partial sums of the norm stay few.
+static int schur_block(const qxd_handle* h, qxd_prec p) {
+  if (h->Ve <= (p == QXD_BF16 ? 65536 : 32768)) return 0;
+  return h->Ve <= (1 << 18) ? 64 : QXD_BLOCK;
+}
+
 template <class T, class SPT, class LKT, class CLT>
 static void launch_schur(qxd_handle* h, int dagger, SPT* out, const SPT* in, SPT* t, const LKT* V, const CLT* He,
-                         const CLT* Hi, double* norm_slot, int slices, hipStream_t s) {
+                         const CLT* Hi, double* norm_slot, int slices, int block, hipStream_t s) {
   const size_t lk_half = (size_t)4 * 9 * h->Ve;
   const LKT* Ve_l = V;
   const LKT* Vo_l = V + lk_half;
-  const int G = div_up(h->Ve, QXD_BLOCK);
+  const int per = block ? block : 64;  // sites of a workgroup
+  const int G = div_up(h->Ve, per);
   Geo g = h->geo;
+  if (g.tchunk > 0) g.tchunk *= QXD_BLOCK / per;  // the walk's windows in sites, whatever the workgroup
   auto pass1 = [&](int tile0, int n) {
     g.tile0 = tile0;
-    if (dagger)
-      hipLaunchKernelGGL((k_schur1<T, SPT, LKT, CLT, true>), dim3(n), dim3(QXD_BLOCK), 0, s, g, in, t, Ve_l, Vo_l, Hi);
-    else
-      hipLaunchKernelGGL((k_schur1<T, SPT, LKT, CLT, false>), dim3(n), dim3(QXD_BLOCK), 0, s, g, in, t, Ve_l, Vo_l, Hi);
+    auto go = [&](auto dag) {
+      constexpr bool D = decltype(dag)::value;
+      if (block == 0)
+        hipLaunchKernelGGL((k_hop4<false, D, false, false, T, SPT, LKT, CLT>), dim3(n), dim3(256), 0, s, g, 1, in,
+                           (const SPT*)nullptr, t, Vo_l, Ve_l, Hi, T(0), (double*)nullptr);
+      else if (block == 64)
+        hipLaunchKernelGGL((k_schur1<64, T, SPT, LKT, CLT, D>), dim3(n), dim3(64), 0, s, g, in, t, Ve_l, Vo_l, Hi);
+      else
+        hipLaunchKernelGGL((k_schur1<QXD_BLOCK, T, SPT, LKT, CLT, D>), dim3(n), dim3(QXD_BLOCK), 0, s, g, in, t, Ve_l,
+                           Vo_l, Hi);
+    };
+    dagger ? go(std::true_type{}) : go(std::false_type{});
   };
   auto pass2 = [&](int tile0, int n) {
     g.tile0 = tile0;
     if (n <= 0) return;
-    if (norm_slot) {
-      if (dagger)
-        hipLaunchKernelGGL((k_schur2<T, SPT, LKT, CLT, true, true>), dim3(n), dim3(QXD_BLOCK), 0, s, g, t, in, out,
-                           Ve_l, Vo_l, He, h->partial);
+    double* part = norm_slot ? h->partial : nullptr;
+    auto go = [&](auto dag, auto nrm) {
+      constexpr bool D = decltype(dag)::value, N = decltype(nrm)::value;
+      if (block == 0)
+        hipLaunchKernelGGL((k_hop4<true, false, D, N, T, SPT, LKT, CLT>), dim3(n), dim3(256), 0, s, g, 0, t, in, out,
+                           Ve_l, Vo_l, He, T(-0.25), part);
+      else if (block == 64)
+        hipLaunchKernelGGL((k_schur2<64, T, SPT, LKT, CLT, D, N>), dim3(n), dim3(64), 0, s, g, t, in, out, Ve_l, Vo_l,
+                           He, part);
       else
-        hipLaunchKernelGGL((k_schur2<T, SPT, LKT, CLT, false, true>), dim3(n), dim3(QXD_BLOCK), 0, s, g, t, in, out,
-                           Ve_l, Vo_l, He, h->partial);
-    } else {
-      if (dagger)
-        hipLaunchKernelGGL((k_schur2<T, SPT, LKT, CLT, true, false>), dim3(n), dim3(QXD_BLOCK), 0, s, g, t, in, out,
-                           Ve_l, Vo_l, He, nullptr);
-      else
-        hipLaunchKernelGGL((k_schur2<T, SPT, LKT, CLT, false, false>), dim3(n), dim3(QXD_BLOCK), 0, s, g, t, in, out,
-                           Ve_l, Vo_l, He, nullptr);
-    }
+        hipLaunchKernelGGL((k_schur2<QXD_BLOCK, T, SPT, LKT, CLT, D, N>), dim3(n), dim3(QXD_BLOCK), 0, s, g, t, in, out,
+                           Ve_l, Vo_l, He, part);
+    };
+    if (norm_slot)
+      dagger ? go(std::true_type{}, std::true_type{}) : go(std::false_type{}, std::true_type{});
+    else
+      dagger ? go(std::true_type{}, std::false_type{}) : go(std::false_type{}, std::false_type{});
   };
   if (slices == 0) {
     g.ntile = 0;
     pass1(0, G);
     pass2(0, G);
   } else {
-    const int T1 = (int)(h->Ve / h->geo.Le0 / QXD_BLOCK);  // tiles per time slice
+    const int T1 = (int)(h->Ve / h->geo.Le0 / per);  // tiles per time slice
     const int C = slices, nchunk = h->geo.Le0 / slices;
     g.ntile = G;
     // chunk k: slices kC - 1 .. (k+1)C - 2 (chunk 0 starts at the last slice);
@@ -303,15 +477,15 @@ qxd_status qxd_schur_apply(qxd_handle* h, qxd_prec p, int dagger, void* out_e, c
   switch (p) {
     case QXD_F64:
       launch_schur<double>(h, dagger, (double2*)out_e, (const double2*)in_e, h->t64, (const double2*)h->V64,
-                           (const double2*)h->He64, (const double2*)h->Hi64, norm_slot, schur_slices(h, p), s);
+                           (const double2*)h->He64, (const double2*)h->Hi64, norm_slot, schur_slices(h, p), schur_block(h, p), s);
       break;
     case QXD_F32:
       launch_schur<float>(h, dagger, (float4*)out_e, (const float4*)in_e, h->t32, (const float2*)h->V32,
-                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), s);
+                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), schur_block(h, p), s);
       break;
     case QXD_BF16:
       launch_schur<float>(h, dagger, (uint4*)out_e, (const uint4*)in_e, h->t16, (const uint32_t*)h->V16,
-                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), s);
+                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), schur_block(h, p), s);
       break;
     default:
       return QXD_EINVAL;
@@ -328,7 +502,7 @@ qxd_status qxd_schur_apply_mixed(qxd_handle* h, int dagger, float4* out_e, const
   QXD_TRY(ensure_copies(h, CP_V16 | CP_HE32 | CP_HI32, s));
   h->geo.tchunk = walk_chunk(h, QXD_F32);
   launch_schur<float>(h, dagger, out_e, in_e, h->t32, (const uint32_t*)h->V16, (const float4*)h->He32,
-                      (const float4*)h->Hi32, norm_slot, schur_slices(h, QXD_F32), s);
+                      (const float4*)h->Hi32, norm_slot, schur_slices(h, QXD_F32), schur_block(h, QXD_F32), s);
   QXD_HIP(hipGetLastError());
   return QXD_OK;
 }
@@ -390,15 +564,15 @@ extern "C" qxd_status qxd_dw_eo_schur_noalloc(qxd_handle* h, qxd_prec p, int dag
   switch (p) {
     case QXD_F64:
       launch_schur<double>(h, dagger ? 1 : 0, (double2*)out_e, (const double2*)in_e, (double2*)t,
-                           (const double2*)h->V64, (const double2*)h->He64, (const double2*)h->Hi64, nullptr, schur_slices(h, p), s);
+                           (const double2*)h->V64, (const double2*)h->He64, (const double2*)h->Hi64, nullptr, schur_slices(h, p), schur_block(h, p), s);
       break;
     case QXD_F32:
       launch_schur<float>(h, dagger ? 1 : 0, (float4*)out_e, (const float4*)in_e, (float4*)t, (const float2*)h->V32,
-                          (const float4*)h->He32, (const float4*)h->Hi32, nullptr, schur_slices(h, p), s);
+                          (const float4*)h->He32, (const float4*)h->Hi32, nullptr, schur_slices(h, p), schur_block(h, p), s);
       break;
     default:
       launch_schur<float>(h, dagger ? 1 : 0, (uint4*)out_e, (const uint4*)in_e, (uint4*)t, (const uint32_t*)h->V16,
-                          (const float4*)h->He32, (const float4*)h->Hi32, nullptr, schur_slices(h, p), s);
+                          (const float4*)h->He32, (const float4*)h->Hi32, nullptr, schur_slices(h, p), schur_block(h, p), s);
       break;
   }
   QXD_HIP(hipGetLastError());
@@ -407,14 +581,22 @@ extern "C" qxd_status qxd_dw_eo_schur_noalloc(qxd_handle* h, qxd_prec p, int dag
 
 template <class T, class SPT, class LKT, class CLT>
 static void launch_dw(qxd_handle* h, SPT* out, const SPT* in, const LKT* V, const CLT* He, const CLT* Ho, int groups,
-                      hipStream_t s) {
-  const size_t lk_half = (size_t)4 * 9 * h->Ve;
-  const size_t sp_half = (size_t)groups * h->Ve;
-  int G = div_up(h->Ve, QXD_BLOCK);
-  hipLaunchKernelGGL((k_dw<T, SPT, LKT, CLT>), dim3(G), dim3(QXD_BLOCK), 0, s, h->geo, 0, in, in + sp_half, out, V,
-                     V + lk_half, He);
-  hipLaunchKernelGGL((k_dw<T, SPT, LKT, CLT>), dim3(G), dim3(QXD_BLOCK), 0, s, h->geo, 1, in + sp_half, in,
-                     out + sp_half, V + lk_half, V, Ho);
+                      int block, hipStream_t s) {
+  const size_t lk = (size_t)4 * 9 * h->Ve, sp = (size_t)groups * h->Ve;
+  const int per = block ? block : 64;
+  const int G = div_up(h->Ve, per);
+  Geo g = h->geo;
+  if (g.tchunk > 0) g.tchunk *= QXD_BLOCK / per;
+  if (block == 0)
+    for (int p = 0; p < 2; ++p)
+      hipLaunchKernelGGL((k_hop4<true, false, false, false, T, SPT, LKT, CLT>), dim3(G), dim3(256), 0, s, g, p,
+                         in + (p ? 0 : sp), in + (p ? sp : 0), out + (p ? sp : 0), V + (p ? lk : 0), V + (p ? 0 : lk),
+                         p ? Ho : He, T(-0.5), (double*)nullptr);
+  else if (block == 64)
+    hipLaunchKernelGGL((k_dw<64, T, SPT, LKT, CLT>), dim3(G, 2), dim3(64), 0, s, g, in, out, V, He, Ho, sp, lk);
+  else
+    hipLaunchKernelGGL((k_dw<QXD_BLOCK, T, SPT, LKT, CLT>), dim3(G, 2), dim3(QXD_BLOCK), 0, s, g, in, out, V, He, Ho,
+                       sp, lk);
 }
 
 extern "C" qxd_status qxd_dw_apply(qxd_handle* h, qxd_prec p, void* out, const void* in, void* stream) {
@@ -424,17 +606,17 @@ extern "C" qxd_status qxd_dw_apply(qxd_handle* h, qxd_prec p, void* out, const v
   switch (p) {
     case QXD_F64:
       launch_dw<double>(h, (double2*)out, (const double2*)in, (const double2*)h->V64, (const double2*)h->He64,
-                        (const double2*)h->Ho64, 12, s);
+                        (const double2*)h->Ho64, 12, schur_block(h, p), s);
       break;
     case QXD_F32:
     case QXD_BF16:
       QXD_TRY(ensure_copies(h, (p == QXD_F32 ? CP_V32 : CP_V16) | CP_HE32 | CP_HO32, s));
       if (p == QXD_F32)
         launch_dw<float>(h, (float4*)out, (const float4*)in, (const float2*)h->V32, (const float4*)h->He32,
-                         (const float4*)h->Ho32, 6, s);
+                         (const float4*)h->Ho32, 6, schur_block(h, p), s);
       else
         launch_dw<float>(h, (uint4*)out, (const uint4*)in, (const uint32_t*)h->V16, (const float4*)h->He32,
-                         (const float4*)h->Ho32, 3, s);
+                         (const float4*)h->Ho32, 3, schur_block(h, p), s);
       break;
     default:
       return QXD_EINVAL;
