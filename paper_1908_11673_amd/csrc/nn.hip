@@ -52,7 +52,6 @@ struct qxd_nn {
   float* y = nullptr;      // training: raw network output (even half field, F32)
   float *dv = nullptr, *dz = nullptr;  // training, residual loss: D_hat u and D_hat^+ D_hat u
   float* part = nullptr;   // weight-gradient partials
-  int nchunk = 0;
   bool blk = false;        // block-tiled convolutions (else per-site gathers)
   int ncu = 1;             // compute units: workgroups of the persistent convolution
 };
@@ -737,14 +736,249 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(Geo g, const uint16_t* __res
   }
 }
 
-// grad[off + (tap cout + co) cin + ci] += sum over chunks (fixed order)
-__global__ void k_wgrad_reduce(const float* __restrict__ part, int nchunk, int cin, int cout, int off,
-                               float* __restrict__ grad) {
+// ---------------------------------------------------------------------------
+// Block-tiled weight gradient, where the 4 x 4 x 4 x 8 blocks divide the
+// lattice.  With r = q + d3 e3, the gradient of tap d is
+//   sum_r g[r - d3 e3][co] in[r + (d0, d1, d2)][ci],
+// so with rows of 8 sites along x3 as the contraction index every operand of
+// `in` is a whole row, whatever the tap, and the shift by d3 falls on g, whose
+// three shifted rows serve all of (d0, d1, d2).  A workgroup takes one d0 (27
+// taps) on a run of blocks: per block it stages the rows of `in` at x0 + d0
+// with their halo in x1 and x2, and those of g with the sites next to their
+// ends, transposed to [row][channel][8 sites] (8 x 8 transposes in registers,
+// so that LDS is written in 16-byte words), the next block's rows being loaded
+// into registers meanwhile.  A step contracts two rows, 16 sites: 27
+// instructions of 32 cycles over four SIMDs against 26.6 kB of LDS reads.
+//
+// The matrix cores bound it: 54 us a layer at 32 x 16^3 (44 GFLOP, 0.81 PFLOP/s;
+// 44 us without the loads of the next block, 36 without its staging and the LDS
+// reads), where transposing every tap's operand through LDS in 2-byte words
+// (k_conv_wgrad) takes 165 (92 in the last layer, over the even sites only).
+// Four waves of seven taps, one a SIMD, take 54 to 61 us however their LDS
+// reads are scheduled.  One d0 a workgroup, so that a partial sum is 108 kB: 256
+// workgroups of all 81 taps would leave 85 MB; summing the partials takes 7.7 us
+// (33 before, over 128 partials of all taps).
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+
+struct WgLds {
+  u4v in[144][NN_C];        // rows (y0, y1, y2) in 4 x 6 x 6, channels swizzled (wg_slot)
+  u4v g[64][NN_C];          // rows (r0, r1, r2) in 4 x 4 x 4
+  uint32_t e[64][NN_C];     // g at x3 = -1 (low half) and x3 = 8 (high half) of each row
+};
+static_assert(NnBlock::B0 == 4 && NnBlock::B1 == 4 && NnBlock::B2 == 4 && NnBlock::B3 == 8, "wgrad tile");
+
+// Where channel ch of a row stands: the 8 channels of a group permuted so that
+// the writes of 8 neighbouring lanes (two rows, four groups) meet all banks.
+__device__ __forceinline__ int wg_slot(int row, int ch) {
+  return (ch & 24) | ((ch & 7) ^ (((row & 1) << 2) | (ch >> 3)));
+}
+
+// v[j]: channels 8 cg .. 8 cg + 7 of site j  ->  L[slot of channel]: sites 0 .. 7
+__device__ __forceinline__ void wg_store8(u4v* L, int row, int cg, const u4v v[8]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    u4v lo, hi;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      lo[j] = __builtin_amdgcn_perm(v[2 * j + 1][k], v[2 * j][k], 0x05040100u);
+      hi[j] = __builtin_amdgcn_perm(v[2 * j + 1][k], v[2 * j][k], 0x07060302u);
+    }
+    L[wg_slot(row, 8 * cg + 2 * k)] = lo;
+    L[wg_slot(row, 8 * cg + 2 * k + 1)] = hi;
+  }
+}
+
+constexpr int kWgWaves = 8;  // of a workgroup, two a SIMD
+
+// A thread's share of the next block: 8-site pieces of 8 channels tid and tid +
+// 512 of the 576 of `in` and the 256 of g, and for the latter the sites next to
+// the row's ends.  Which of the two a piece belongs to is uniform in a wave.
+struct WgRegs {
+  u4v v[2][8], e[2];
+};
+constexpr int kWgIn = 144 * 4, kWgPieces = kWgIn + 64 * 4;
+
+__device__ __forceinline__ void wg_load(const Geo& g, const uint16_t* __restrict__ gq, const uint16_t* __restrict__ in,
+                                        int o0, int o1, int o2, int o3, int d0, WgRegs& R) {
+  const int cg = threadIdx.x & 3;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int piece = threadIdx.x + 64 * kWgWaves * u;
+    if (piece >= kWgPieces) break;
+    const bool of_g = piece >= kWgIn;
+    const int row = (of_g ? piece - kWgIn : piece) >> 2;
+    int x0, x1, x2;
+    if (of_g) {
+      x0 = o0 + (row >> 4), x1 = o1 + ((row >> 2) & 3), x2 = o2 + (row & 3);
+    } else {
+      x0 = o0 + row / 36 + d0, x1 = o1 + row / 6 % 6 - 1, x2 = o2 + row % 6 - 1;
+      x0 = x0 < 0 ? x0 + g.Le0 : (x0 >= g.Le0 ? x0 - g.Le0 : x0);
+      x1 = x1 < 0 ? x1 + g.Le1 : (x1 >= g.Le1 ? x1 - g.Le1 : x1);
+      if (x2 < 0 || x2 >= g.Le2) {
+        x2 = x2 < 0 ? x2 + g.Le2 : x2 - g.Le2;
+        if (g.cstar >= 2) x1 = geo_mirror_x1(g, x1);
+      }
+    }
+    const int p = (x0 + x1 + x2) & 1, hb = geo_half(g, x0, x1, x2, o3);
+    const uint16_t* f = (of_g ? gq : in) + 8 * cg;
+    const uint16_t* f0 = f + ((size_t)p * g.Ve + hb) * NN_C;        // sites 0, 2, 4, 6
+    const uint16_t* f1 = f + ((size_t)(1 - p) * g.Ve + hb) * NN_C;  // sites 1, 3, 5, 7
+#pragma unroll
+    for (int j = 0; j < 8; ++j) R.v[u][j] = *reinterpret_cast<const u4v*>(((j & 1) ? f1 : f0) + (j >> 1) * NN_C);
+    if (u == 1 && of_g) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        int y1 = x1, y3 = k ? o3 + NnBlock::B3 : o3 - 1;
+        if (y3 < 0 || y3 >= g.Le3) {
+          y3 = y3 < 0 ? y3 + g.Le3 : y3 - g.Le3;
+          if (g.cstar >= 3) y1 = geo_mirror_x1(g, y1);
+        }
+        const size_t q = (size_t)((x0 + y1 + x2 + y3) & 1) * g.Ve + geo_half(g, x0, y1, x2, y3);
+        R.e[k] = *reinterpret_cast<const u4v*>(f + q * NN_C);
+      }
+    }
+  }
+}
+static_assert(kWgIn >= 64 * kWgWaves && kWgPieces <= 2 * 64 * kWgWaves && kWgIn % 64 == 0, "pieces of a thread");
+
+__device__ __forceinline__ void wg_stage(WgLds& L, const WgRegs& R) {
+  const int cg = threadIdx.x & 3;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int piece = threadIdx.x + 64 * kWgWaves * u;
+    if (piece >= kWgPieces) break;
+    const bool of_g = piece >= kWgIn;
+    const int row = (of_g ? piece - kWgIn : piece) >> 2;
+    wg_store8(of_g ? L.g[row] : L.in[row], row, cg, R.v[u]);
+    if (u == 1 && of_g) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        L.e[row][8 * cg + 2 * k] = __builtin_amdgcn_perm(R.e[1][k], R.e[0][k], 0x05040100u);
+        L.e[row][8 * cg + 2 * k + 1] = __builtin_amdgcn_perm(R.e[1][k], R.e[0][k], 0x07060302u);
+      }
+    }
+  }
+}
+
+// Wave w takes (d1, d2) pair w with its three d3, and waves 0, 1, 2 one d3 each
+// of the ninth pair: seven taps (the last six) a SIMD.  The accumulators stand
+// for d3 = -1, 0, 1 and the ninth pair.
+__device__ __forceinline__ void wg_contract(const WgLds& L, int w, f16v (&acc)[4]) {
+  const int l = threadIdx.x & 63, ch = l & 31, hf = l >> 5;
+  const int p1 = w / 3, p2 = w % 3;  // 1 + d1, 1 + d2
+  // this lane's channel in rows r2 + hf of g and r2 + hf + p2 of in (r2 even)
+  const char* gr = reinterpret_cast<const char*>(L.g) + hf * (NN_C * 16) + wg_slot(hf, ch) * 16;
+  const char* er = reinterpret_cast<const char*>(L.e) + hf * (NN_C * 4) + ch * 4;
+  const char* in0 = reinterpret_cast<const char*>(L.in) + (p1 * 6 + p2 + hf) * (NN_C * 16) + wg_slot(hf + p2, ch) * 16;
+  const char* in8 = reinterpret_cast<const char*>(L.in) + (2 * 6 + 2 + hf) * (NN_C * 16) + wg_slot(hf, ch) * 16;
+  struct Ops {
+    u4v c;
+    uint32_t e;
+    bf16x8 b, b8;
+  };
+  auto read = [&](int r0, int st) {
+    const int r1 = st >> 1, r2 = 2 * (st & 1);
+    const int go = r0 * 16 + r1 * 4 + r2, io = (r0 * 36 + r1 * 6 + r2) * (NN_C * 16);
+    Ops o;
+    o.c = *reinterpret_cast<const u4v*>(gr + go * (NN_C * 16));
+    o.e = *reinterpret_cast<const uint32_t*>(er + go * (NN_C * 4));
+    o.b = *reinterpret_cast<const bf16x8*>(in0 + io);
+    o.b8 = *reinterpret_cast<const bf16x8*>(in8 + io);
+    return o;
+  };
+  auto mfma = [](u4v a, bf16x8 b, f16v& c) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), b, c, 0, 0, 0);
+  };
+  // the rows of step k + 1 are requested before step k is contracted (left to
+  // itself the compiler requests them next to their use)
+  Ops cur = read(0, 0);
+#pragma unroll 1
+  for (int r0 = 0; r0 < 4; ++r0) {
+#pragma unroll
+    for (int st = 0; st < 8; ++st) {
+      const Ops nxt = st < 7 ? read(r0, st + 1) : read(min(r0 + 1, 3), 0);
+      __builtin_amdgcn_sched_barrier(0);
+      // g one site to the right (d3 = -1), in place, one to the left (d3 = +1)
+      const u4v c = cur.c;
+      const uint32_t m01 = __builtin_amdgcn_alignbit(c[1], c[0], 16), m12 = __builtin_amdgcn_alignbit(c[2], c[1], 16),
+                     m23 = __builtin_amdgcn_alignbit(c[3], c[2], 16);
+      const u4v lo = u4v{m01, m12, m23, __builtin_amdgcn_perm(cur.e, c[3], 0x07060302u)};
+      const u4v hi = u4v{__builtin_amdgcn_perm(c[0], cur.e, 0x05040100u), m01, m12, m23};
+      mfma(c, cur.b, acc[1]);
+      mfma(lo, cur.b, acc[0]);
+      mfma(hi, cur.b, acc[2]);
+      if (w < 3) mfma(w == 0 ? lo : w == 1 ? c : hi, cur.b8, acc[3]);
+      cur = nxt;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+// The work is the list of (d0, block) items, d0 slowest; workgroup u takes items
+// run u .. run u + run - 1 and leaves a partial sum for each d0 among them, in
+// slot u - wg_first(d0) of that d0.
+__host__ __device__ inline int wg_first(int nblk, int run, int i0) { return (int)((int64_t)i0 * nblk / run); }
+
+__global__ __launch_bounds__(64 * kWgWaves, 2) void k_wgrad_blk(Geo g, int nblk, int run, const uint16_t* __restrict__ gq,
+                                                      const uint16_t* __restrict__ in, float* __restrict__ part) {
+  using SH = NnBlock;
+  __shared__ WgLds L;
+  // neighbouring runs on one XCD
+  const int unit = site_tile(blockIdx.x, gridDim.x, -1);
+  const int n1 = g.Le1 / SH::B1, n2 = g.Le2 / SH::B2, n3 = g.Le3 / SH::B3;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+  const int beg = unit * run, end = min(3 * nblk, beg + run);
+  WgRegs R;
+  auto load = [&](int item) {
+    const int d0 = item / nblk - 1, b = item % nblk;
+    const int c3 = b % n3, c2 = b / n3 % n2, c1 = b / (n3 * n2) % n1, c0 = b / (n3 * n2 * n1);
+    wg_load(g, gq, in, c0 * SH::B0, c1 * SH::B1, c2 * SH::B2, c3 * SH::B3, d0, R);
+  };
+  load(beg);
+  for (int first = beg; first < end;) {
+    const int i0 = first / nblk, last = min(end, (i0 + 1) * nblk);
+    f16v acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+    for (int it = first; it < last; ++it) {
+      wg_stage(L, R);
+      __syncthreads();
+      if (it + 1 < end) load(it + 1);
+      wg_contract(L, w, acc);
+      __syncthreads();  // every wave is done with the rows
+    }
+    float* o = part + ((size_t)(unit - wg_first(nblk, run, i0)) * NN_TAPS + 27 * i0) * (NN_C * NN_C);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (t == 3 && w >= 3) break;
+      const int tap = t < 3 ? 3 * w + t : 24 + w;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int row = (i / 4) * 8 + (l >> 5) * 4 + (i & 3);
+        o[tap * (NN_C * NN_C) + row * NN_C + (l & 31)] = acc[t][i];
+      }
+    }
+    first = last;
+  }
+}
+
+// grad[off + (tap cout + co) cin + ci] += sum over the partial sums of the tap
+// (fixed order): nchunk of them, or (run > 0) those of k_wgrad_blk
+__global__ void k_wgrad_reduce(const float* __restrict__ part, int nchunk, int nblk, int run, int cin, int cout,
+                               int off, float* __restrict__ grad) {
   int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= NN_TAPS * cout * cin) return;
   int tap = t / (cout * cin), co = (t / cin) % cout, ci = t % cin;
+  if (run > 0) {
+    const int i0 = tap / 27;
+    nchunk = (int)(((int64_t)(i0 + 1) * nblk - 1) / run) - wg_first(nblk, run, i0) + 1;
+  }
+  const float* p = part + (size_t)tap * (NN_C * NN_C) + co * NN_C + ci;
   double s = 0.0;
-  for (int c = 0; c < nchunk; ++c) s += part[((size_t)c * NN_TAPS + tap) * (NN_C * NN_C) + co * NN_C + ci];
+#pragma unroll 16
+  for (int c = 0; c < nchunk; ++c) s += p[(size_t)c * NN_TAPS * NN_C * NN_C];
   grad[off + t] += (float)s;
 }
 
@@ -847,17 +1081,22 @@ static qxd_status nn_alloc_act(qxd_nn* net, hipStream_t s) {
   return QXD_OK;
 }
 
+// Items of a workgroup of k_wgrad_blk: one round of the chip (a workgroup a
+// CU), and at most 8 blocks (4096 sites) in one FP32 sum.
+static int wgrad_run(const qxd_nn* net, int nblk) { return std::min(8, div_up(3 * (int64_t)nblk, net->ncu)); }
+
 static qxd_status nn_alloc_train(qxd_nn* net, hipStream_t s) {
   QXD_TRY(nn_alloc_act(net, s));
   if (net->g3) return QXD_OK;
   qxd_handle* h = net->h;
   size_t bytes = (size_t)h->V * NN_C * sizeof(uint16_t);
-  net->nchunk = div_up(h->V, kWgChunk);
+  const int nblk = (int)(h->V / NN_BLK_SITES);
+  const int nchunk = net->blk ? div_up(nblk, wgrad_run(net, nblk)) + 1 : div_up(h->V, kWgChunk);
   if (!dev_alloc(&net->g3, bytes) || !dev_alloc(&net->gA, bytes) || !dev_alloc(&net->gB, bytes) ||
       !dev_alloc(&net->y, (size_t)h->Ve * 24 * sizeof(float)) ||
       !dev_alloc(&net->dv, (size_t)h->Ve * 24 * sizeof(float)) ||
       !dev_alloc(&net->dz, (size_t)h->Ve * 24 * sizeof(float)) ||
-      !dev_alloc(&net->part, (size_t)net->nchunk * NN_TAPS * NN_C * NN_C * sizeof(float))) {
+      !dev_alloc(&net->part, (size_t)nchunk * NN_TAPS * NN_C * NN_C * sizeof(float))) {
     nn_free_all({(void**)&net->g3, (void**)&net->gA, (void**)&net->gB, (void**)&net->y, (void**)&net->dv,
                  (void**)&net->dz, (void**)&net->part});
     return QXD_ENOMEM;
@@ -888,6 +1127,26 @@ static qxd_status nn_forward(qxd_handle* h, qxd_nn* net, const float4* r, float*
 qxd_status nn_apply_internal(qxd_handle* h, qxd_nn* net, float4* out_e, const float4* in_e, hipStream_t s) {
   if (!net || net->h != h) return QXD_EINVAL;
   return nn_forward(h, net, in_e, reinterpret_cast<float*>(out_e), true, s);
+}
+
+// grad += the weight gradient of `layer` from the output gradient gq (zero
+// beyond its first nq sites) and the layer's input
+static void wgrad(qxd_handle* h, qxd_nn* net, const uint16_t* gq, const uint16_t* in, int nq, int layer, hipStream_t s) {
+  const int cin = kCin[layer], cout = kCout[layer];
+  int nchunk = 0, nblk = 0, run = 0;
+  if (net->blk) {
+    nblk = (int)(h->V / NN_BLK_SITES);
+    run = wgrad_run(net, nblk);
+    hipLaunchKernelGGL(k_wgrad_blk, dim3(div_up(3 * (int64_t)nblk, run)), dim3(64 * kWgWaves), 0, s, h->geo, nblk, run, gq, in,
+                       net->part);
+  } else {
+    nchunk = div_up(nq, kWgChunk);
+    hipLaunchKernelGGL(k_conv_wgrad, dim3(nchunk, div_up(NN_TAPS, 4)), dim3(256), 0, s, h->geo, gq, in, nq, kWgChunk,
+                       net->part);
+  }
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3(div_up(NN_TAPS * cout * cin, 256)), dim3(256), 0, s, net->part, nchunk, nblk,
+                     run, cin,
+                     cout, kOff[layer], net->grad);
 }
 
 // loss of one pair (r, e) and, with `backward`, accumulation of its weight
@@ -925,24 +1184,17 @@ static qxd_status nn_pair(qxd_handle* h, qxd_nn* net, const float4* r, const flo
     }
   }
   if (!backward) return QXD_OK;
-  // layer 3: weight gradient over the even sites, data gradient masked by a2 > 0
-  dim3 wg(net->nchunk, div_up(NN_TAPS, 4));
-  dim3 wg_e(div_up(h->Ve, kWgChunk), div_up(NN_TAPS, 4));
-  hipLaunchKernelGGL(k_conv_wgrad, wg_e, dim3(256), 0, s, h->geo, net->g3, net->a2, (int)h->Ve, kWgChunk, net->part);
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3(div_up(NN_TAPS * 24 * 32, 256)), dim3(256), 0, s, net->part,
-                     (int)wg_e.x, 32, 24, kOff[2], net->grad);
+  // layer 3 (its output gradient g3 vanishes on the odd sites): weight
+  // gradient, then the data gradient masked by a2 > 0
+  wgrad(h, net, net->g3, net->a2, (int)h->Ve, 2, s);
   conv_launch(h, 2, net->g3, net->wa, (int)h->V, EPI_MASK, net->gA, nullptr, net->a2, nullptr, 0, s, nullptr, 0.f,
               nullptr, 0, net);
   // layer 2
-  hipLaunchKernelGGL(k_conv_wgrad, wg, dim3(256), 0, s, h->geo, net->gA, net->a1, (int)h->V, kWgChunk, net->part);
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3(div_up(NN_TAPS * 32 * 32, 256)), dim3(256), 0, s, net->part, net->nchunk,
-                     32, 32, kOff[1], net->grad);
+  wgrad(h, net, net->gA, net->a1, (int)h->V, 1, s);
   conv_launch(h, 1, net->gA, net->wa, (int)h->V, EPI_MASK, net->gB, nullptr, net->a1, nullptr, 0, s, nullptr, 0.f,
               nullptr, 0, net);
   // layer 1
-  hipLaunchKernelGGL(k_conv_wgrad, wg, dim3(256), 0, s, h->geo, net->gB, net->a0, (int)h->V, kWgChunk, net->part);
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3(div_up(NN_TAPS * 32 * 24, 256)), dim3(256), 0, s, net->part, net->nchunk,
-                     24, 32, kOff[0], net->grad);
+  wgrad(h, net, net->gB, net->a0, (int)h->V, 0, s);
   QXD_HIP(hipGetLastError());
   return QXD_OK;
 }
