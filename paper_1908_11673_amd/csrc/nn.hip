@@ -1338,12 +1338,17 @@ extern "C" qxd_status qxd_nn_loss_grad(qxd_handle* h, qxd_nn* net, const void* r
   QXD_HIP(hipMemsetAsync(net->grad, 0, QXD_NN_NWEIGHTS * 4, s));
   size_t half = (size_t)6 * h->Ve;
   double total = 0.0;
-  for (int i = 0; i < n; ++i) {
-    QXD_TRY(nn_pair(h, net, (const float4*)r + i * half, (const float4*)e + i * half, 1.0 / n, S_NN, loss_kind, true,
-                    s));
-    QXD_HIP(hipMemcpyAsync(h->scal_host + S_NN, h->scal + S_NN, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
+  const int base = S_NN + 8;
+  for (int i0 = 0; i0 < n; i0 += 64) {  // the host reads the losses of 64 pairs at once
+    const int m = std::min(64, n - i0);
+    for (int k = 0; k < m; ++k) {
+      const size_t i = i0 + k;
+      QXD_TRY(nn_pair(h, net, (const float4*)r + i * half, (const float4*)e + i * half, 1.0 / n, base + 3 * k,
+                      loss_kind, true, s));
+    }
+    QXD_HIP(hipMemcpyAsync(h->scal_host + base, h->scal + base, 3 * m * sizeof(double), hipMemcpyDeviceToHost, s));
     QXD_HIP(hipStreamSynchronize(s));
-    total += pair_loss(h, S_NN, loss_kind) / n;
+    for (int k = 0; k < m; ++k) total += pair_loss(h, base + 3 * k, loss_kind) / n;
   }
   if (loss) *loss = total;
   if (grad) {
