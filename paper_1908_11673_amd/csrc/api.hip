@@ -30,6 +30,7 @@ static void release(qxd_handle* h) {
   for (int i = 0; i < 64; ++i)
     if (h->ws[i]) (void)hipFree(h->ws[i]);
   if (h->scal_host) (void)hipHostFree(h->scal_host);
+  if (h->step_done) (void)hipEventDestroy(h->step_done);
 }
 
 extern "C" qxd_status qxd_create(const qxd_geom* g, qxd_handle** out) {

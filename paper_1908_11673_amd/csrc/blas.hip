@@ -7,6 +7,9 @@
 // a fixed order, so results are bitwise reproducible run to run.  Scalars such as
 // CG's alpha and beta are read by the update kernels straight from device
 // memory; the host never waits inside an iteration.
+#include <algorithm>
+#include <type_traits>
+
 #include "blas.hpp"
 
 __device__ inline double red_block(double v, double* sh) {
@@ -20,6 +23,56 @@ __device__ inline double red_block(double v, double* sh) {
     for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s += sh[i];
   return s;
 }
+
+// Sums of several values over a wavefront at once.  With C > 1 values left, the
+// two halves of the lanes (by bit M) exchange the half of the values that the
+// other one keeps, so the C values cost C - 1 exchanges in all instead of C
+// log2(64) ; then the one left is summed over the remaining bits.  Returns the
+// total of value wave_sums_index(lane).
+template <int C, int M>
+__device__ __forceinline__ double wave_sums(double* v) {
+  const bool up = (threadIdx.x & M) != 0;
+  if constexpr (C > 1) {
+#pragma unroll
+    for (int i = 0; i < C / 2; ++i) {
+      const double keep = up ? v[i + C / 2] : v[i], send = up ? v[i] : v[i + C / 2];
+      v[i] = keep + __shfl_xor(send, M);
+    }
+    if constexpr (M > 1) return wave_sums<C / 2, M / 2>(v);
+  } else {
+    v[0] += __shfl_xor(v[0], M);
+    if constexpr (M > 1) return wave_sums<1, M / 2>(v);
+  }
+  return v[0];
+}
+constexpr int pow2_from(int n) { return n <= 1 ? 1 : 2 * pow2_from((n + 1) / 2); }
+
+// partial[j gridDim.x + blockIdx.x] = the workgroup's sum of a[j], j < NV: one
+// barrier.  (A block reduction per value, two barriers each, took 15 us of a
+// launch for the 30 values of 15 dots.)
+template <int NV>
+__device__ __forceinline__ void block_sums(const double* a, double* __restrict__ partial) {
+  constexpr int P = pow2_from(NV), W = QXD_BLOCK / 64;
+  static_assert(P <= 64, "values of a wave reduction");
+  __shared__ double sh[W][P];
+  double v[P];
+#pragma unroll
+  for (int j = 0; j < P; ++j) v[j] = j < NV ? a[j] : 0.0;
+  const double t = wave_sums<P, 32>(v);
+  const int lane = threadIdx.x & 63;
+  if ((lane & (64 / P - 1)) == 0) sh[threadIdx.x >> 6][lane / (64 / P)] = t;
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) s += sh[w][threadIdx.x];
+    partial[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = s;
+  }
+}
+
+// Workgroups of a streaming kernel over n elements: at most QXD_NRED, and no
+// more than have an element (the others' sums would be zeros).
+static int nred(size_t n) { return (int)std::max<size_t>(1, std::min<size_t>(QXD_NRED, (n + QXD_BLOCK - 1) / QXD_BLOCK)); }
 
 // ---- word helpers ---------------------------------------------------------
 
@@ -94,14 +147,18 @@ struct W2 {
 // One workgroup per value.  Latency bound (a few loads a work-item and one
 // block reduction): about 3 us whatever nvals, where one workgroup taking the
 // values in turn needed 45 us for the 30 values of 15 dots.
+// host: also written there (pinned memory), unless null.
 __global__ __launch_bounds__(QXD_BLOCK) void k_final_sum(const double* __restrict__ partial, int n, int stride,
-                                                         double* __restrict__ out) {
+                                                         double* __restrict__ out, double* __restrict__ host) {
   __shared__ double sh[QXD_BLOCK / 64];
   const int v = blockIdx.x;
   double a = 0.0;
   for (int i = threadIdx.x; i < n; i += QXD_BLOCK) a += partial[(size_t)v * stride + i];
   double s = red_block(a, sh);
-  if (threadIdx.x == 0) out[v] = s;
+  if (threadIdx.x == 0) {
+    out[v] = s;
+    if (host) host[v] = s;
+  }
 }
 
 template <class VT>
@@ -116,14 +173,10 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_norm2(const VT* __restrict__ x, s
 template <class VT>
 __global__ __launch_bounds__(QXD_BLOCK) void k_cdot(const VT* __restrict__ x, const VT* __restrict__ y, size_t n,
                                                     double* __restrict__ partial) {
-  __shared__ double sh[QXD_BLOCK / 64];
-  double re = 0.0, im = 0.0;
+  double a[2] = {0.0, 0.0};
   stream_for(n, [&](size_t i) { return W2<VT>{ld_stream(&x[i]), ld_stream(&y[i])}; },
-             [&](size_t, W2<VT> v) { wcdot(v.a, v.b, re, im); });
-  double s = red_block(re, sh);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
-  s = red_block(im, sh);
-  if (threadIdx.x == 0) partial[gridDim.x + blockIdx.x] = s;
+             [&](size_t, W2<VT> v) { wcdot(v.a, v.b, a[0], a[1]); });
+  block_sums<2>(a, partial);
 }
 
 // CG: alpha = zz / ww; x += alpha p; r -= alpha w; partial |r|^2
@@ -186,10 +239,9 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_sub_norm(VT* __restrict__ r, cons
 template <class VT, int K>
 __global__ __launch_bounds__(QXD_BLOCK) void k_mdot(Ptrs basis, const VT* __restrict__ v, size_t n,
                                                     double* __restrict__ partial) {
-  __shared__ double sh[QXD_BLOCK / 64];
-  double re[K > 0 ? K : 1], im[K > 0 ? K : 1];
+  double d[2 * K];
 #pragma unroll
-  for (int j = 0; j < K; ++j) re[j] = im[j] = 0.0;
+  for (int j = 0; j < 2 * K; ++j) d[j] = 0.0;
   GRID_STRIDE(i, n) {
     VT vi = ld_stream(&v[i]);
 #pragma unroll
@@ -200,82 +252,82 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_mdot(Ptrs basis, const VT* __rest
         if (j0 + j < K) bj[j] = ld_stream(&((const VT*)basis.p[j0 + j])[i]);
 #pragma unroll
       for (int j = 0; j < QXD_KGROUP; ++j)
-        if (j0 + j < K) wcdot(bj[j], vi, re[j0 + j], im[j0 + j]);
+        if (j0 + j < K) wcdot(bj[j], vi, d[2 * (j0 + j)], d[2 * (j0 + j) + 1]);
     }
   }
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    double s = red_block(re[j], sh);
-    if (threadIdx.x == 0) partial[(size_t)(2 * j) * gridDim.x + blockIdx.x] = s;
-    s = red_block(im[j], sh);
-    if (threadIdx.x == 0) partial[(size_t)(2 * j + 1) * gridDim.x + blockIdx.x] = s;
-  }
+  block_sums<2 * K>(d, partial);
 }
 
-// v -= sum_{j < K} c_j basis_j (c complex at coef[2j], coef[2j+1]); partial |v|^2
-template <class VT, int K>
-__global__ __launch_bounds__(QXD_BLOCK) void k_mupdate(VT* __restrict__ v, Ptrs basis,
-                                                       const double* __restrict__ coef, size_t n,
-                                                       double* __restrict__ partial) {
-  __shared__ double sh[QXD_BLOCK / 64];
-  double a = 0.0;
-  GRID_STRIDE(i, n) {
-    VT vi = ld_stream(&v[i]);
-#pragma unroll
-    for (int j0 = 0; j0 < K; j0 += QXD_KGROUP) {
-      VT bj[QXD_KGROUP];
-#pragma unroll
-      for (int j = 0; j < QXD_KGROUP; ++j)
-        if (j0 + j < K) bj[j] = ld_stream(&((const VT*)basis.p[j0 + j])[i]);
-#pragma unroll
-      for (int j = 0; j < QXD_KGROUP; ++j)
-        if (j0 + j < K) vi = wcaxpy(vi, -coef[2 * (j0 + j)], -coef[2 * (j0 + j) + 1], bj[j]);
-    }
-    st_stream(&v[i], vi);
-    a += wnorm2(vi);
-  }
-  double s = red_block(a, sh);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
-}
-
-// v *= 1/sqrt(scal[i_n2]); partial (v, r).  A norm that is zero or not finite
-// (a Krylov breakdown, e.g. on a vanishing source) sets v = 0 instead, so that
-// the update that follows leaves the residual unchanged.
-template <class VT>
-__global__ __launch_bounds__(QXD_BLOCK) void k_scale_cdot(VT* __restrict__ v, const VT* __restrict__ r, size_t n,
-                                                          const double* __restrict__ scal, int i_n2,
+// One Gram-Schmidt update of GCR: v -= sum_{j < K} c_j basis_j (c complex at
+// coef[2j], coef[2j+1]), and with Z also z -= sum_j c_j zbasis_j; partials of
+// |v|^2 and (v, r), so that the normalisation and the residual update that
+// follow (k_gcr_step) need no pass of their own over v and r.
+template <class VT, int K, bool Z>
+__global__ __launch_bounds__(QXD_BLOCK) void k_gcr_update(VT* __restrict__ v, Ptrs basis, VT* __restrict__ z,
+                                                          Ptrs zbasis, const double* __restrict__ coef,
+                                                          const VT* __restrict__ r, size_t n,
                                                           double* __restrict__ partial) {
+  double a[3] = {0.0, 0.0, 0.0};
+  GRID_STRIDE(i, n) {
+    VT vi = ld_stream(&v[i]);
+    const VT ri = ld_stream(&r[i]);
+    VT zi;
+    if (Z) zi = ld_stream(&z[i]);
+#pragma unroll
+    for (int j0 = 0; j0 < K; j0 += QXD_KGROUP) {
+      VT bj[QXD_KGROUP], zj[QXD_KGROUP];
+#pragma unroll
+      for (int j = 0; j < QXD_KGROUP; ++j)
+        if (j0 + j < K) {
+          bj[j] = ld_stream(&((const VT*)basis.p[j0 + j])[i]);
+          if (Z) zj[j] = ld_stream(&((const VT*)zbasis.p[j0 + j])[i]);
+        }
+#pragma unroll
+      for (int j = 0; j < QXD_KGROUP; ++j)
+        if (j0 + j < K) {
+          const double cr = -coef[2 * (j0 + j)], ci = -coef[2 * (j0 + j) + 1];
+          vi = wcaxpy(vi, cr, ci, bj[j]);
+          if (Z) zi = wcaxpy(zi, cr, ci, zj[j]);
+        }
+    }
+    if (K > 0) {
+      st_stream(&v[i], vi);
+      if (Z) st_stream(&z[i], zi);
+    }
+    a[0] += wnorm2(vi);
+    wcdot(vi, ri, a[1], a[2]);
+  }
+  block_sums<3>(a, partial);
+}
+
+// The rest of a GCR step, from |v|^2 and (v, r) at dots: v /= |v|, r -= (v, r) v,
+// the new r also to r_copy unless that is null; with z: z /= |v|, x += (v, r) z.
+// Partial |r|^2.  A norm that is zero or not finite (a Krylov breakdown, e.g. on
+// a vanishing source) sets v (and z) to zero instead, which leaves r (and x)
+// unchanged.
+template <class VT>
+__global__ __launch_bounds__(QXD_BLOCK) void k_gcr_step(VT* __restrict__ v, VT* __restrict__ r, size_t n,
+                                                        const double* __restrict__ dots, double* __restrict__ partial,
+                                                        VT* __restrict__ r_copy, VT* __restrict__ z,
+                                                        VT* __restrict__ x) {
   __shared__ double sh[QXD_BLOCK / 64];
-  const double n2 = scal[i_n2];
+  const double n2 = dots[0];
   const bool ok = n2 > 0.0 && n2 < INFINITY;
   const double sc = ok ? 1.0 / sqrt(n2) : 0.0;
-  double re = 0.0, im = 0.0;
-  stream_for(n, [&](size_t i) { return W2<VT>{ld_stream(&v[i]), ld_stream(&r[i])}; },
-             [&](size_t i, W2<VT> w) {
-               VT vi = ok ? wscale(w.a, sc) : VT{};
-               st_stream(&v[i], vi);
-               wcdot(vi, w.b, re, im);
-             });
-  double s = red_block(re, sh);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
-  s = red_block(im, sh);
-  if (threadIdx.x == 0) partial[gridDim.x + blockIdx.x] = s;
-}
-
-// r -= c v (c complex at scal[i_c]), also written to r_copy unless that is
-// null; partial |r|^2
-template <class VT>
-__global__ __launch_bounds__(QXD_BLOCK) void k_r_update(VT* __restrict__ r, const VT* __restrict__ v, size_t n,
-                                                        const double* __restrict__ scal, int i_c,
-                                                        double* __restrict__ partial, VT* __restrict__ r_copy) {
-  __shared__ double sh[QXD_BLOCK / 64];
-  double cr = scal[i_c], ci = scal[i_c + 1];
+  const double cr = ok ? sc * dots[1] : 0.0, ci = ok ? sc * dots[2] : 0.0;
   double a = 0.0;
   stream_for(n, [&](size_t i) { return W2<VT>{ld_stream(&r[i]), ld_stream(&v[i])}; },
              [&](size_t i, W2<VT> w) {
-               VT ri = wcaxpy(w.a, -cr, -ci, w.b);
+               const VT vi = ok ? wscale(w.b, sc) : VT{};
+               st_stream(&v[i], vi);
+               const VT ri = wcaxpy(w.a, -cr, -ci, vi);
                st_stream(&r[i], ri);
                if (r_copy) st_stream(&r_copy[i], ri);
+               if (z) {
+                 const VT zi = ok ? wscale(ld_stream(&z[i]), sc) : VT{};
+                 st_stream(&z[i], zi);
+                 st_stream(&x[i], wcaxpy(ld_stream(&x[i]), cr, ci, zi));
+               }
                a += wnorm2(ri);
              });
   double s = red_block(a, sh);
@@ -349,35 +401,35 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_up_acc(double2* __restrict__ x, c
 
 // ---- host launchers -------------------------------------------------------
 
-void launch_final_sum(const double* partial, int n, int nvals, int stride, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_final_sum, dim3(nvals), dim3(QXD_BLOCK), 0, s, partial, n, stride, out);
+void launch_final_sum(const double* partial, int n, int nvals, int stride, double* out, hipStream_t s, double* host) {
+  hipLaunchKernelGGL(k_final_sum, dim3(nvals), dim3(QXD_BLOCK), 0, s, partial, n, stride, out, host);
 }
 
 template <class VT>
 void blas_norm2(qxd_handle* h, const VT* x, size_t n, double* slot, hipStream_t s) {
-  hipLaunchKernelGGL(k_norm2<VT>, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, x, n, h->partial);
-  launch_final_sum(h->partial, QXD_NRED, 1, QXD_NRED, slot, s);
+  hipLaunchKernelGGL(k_norm2<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, x, n, h->partial);
+  launch_final_sum(h->partial, nred(n), 1, nred(n), slot, s);
 }
 template <class VT>
 void blas_cdot(qxd_handle* h, const VT* x, const VT* y, size_t n, double* slot, hipStream_t s) {
-  hipLaunchKernelGGL(k_cdot<VT>, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, x, y, n, h->partial);
-  launch_final_sum(h->partial, QXD_NRED, 2, QXD_NRED, slot, s);
+  hipLaunchKernelGGL(k_cdot<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, x, y, n, h->partial);
+  launch_final_sum(h->partial, nred(n), 2, nred(n), slot, s);
 }
 template <class VT>
 void blas_cg_xr(qxd_handle* h, VT* x, VT* r, const VT* p, const VT* w, size_t n, int i_zz, int i_ww, int i_rr,
                 hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_xr<VT>, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, x, r, p, w, n, h->scal, i_zz, i_ww,
+  hipLaunchKernelGGL(k_cg_xr<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, x, r, p, w, n, h->scal, i_zz, i_ww,
                      h->partial);
-  launch_final_sum(h->partial, QXD_NRED, 1, QXD_NRED, h->scal + i_rr, s);
+  launch_final_sum(h->partial, nred(n), 1, nred(n), h->scal + i_rr, s);
 }
 template <class VT>
 void blas_cg_p(qxd_handle* h, VT* p, const VT* z, size_t n, int i_new, int i_old, hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_p<VT>, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, p, z, n, h->scal, i_new, i_old);
+  hipLaunchKernelGGL(k_cg_p<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, p, z, n, h->scal, i_new, i_old);
 }
 template <class VT>
 void blas_sub_norm(qxd_handle* h, VT* r, const VT* b, const VT* w, size_t n, double* slot, hipStream_t s) {
-  hipLaunchKernelGGL(k_sub_norm<VT>, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, r, b, w, n, h->partial);
-  launch_final_sum(h->partial, QXD_NRED, 1, QXD_NRED, slot, s);
+  hipLaunchKernelGGL(k_sub_norm<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, r, b, w, n, h->partial);
+  launch_final_sum(h->partial, nred(n), 1, nred(n), slot, s);
 }
 // one case per basis size 0 .. QXD_MAXKV
 #define QXD_K_CASES(X)                                                                                         \
@@ -386,44 +438,53 @@ void blas_sub_norm(qxd_handle* h, VT* r, const VT* b, const VT* w, size_t n, dou
 static_assert(QXD_MAXKV == 32, "QXD_K_CASES lists the basis sizes 0 .. QXD_MAXKV");
 
 template <class VT>
-void blas_mdot(qxd_handle* h, const Ptrs& basis, int k, const VT* v, size_t n, double* slots, hipStream_t s) {
-  if (k == 0) return;  // no dots
+void blas_mdot(qxd_handle* h, const Ptrs& basis, int k, const VT* v, size_t n, double* slots, hipStream_t s,
+               double* host) {
+  if (k < 1 || k > QXD_MAXKV) return;  // no dots
+  const int G = nred(n);
   switch (k) {
 #define QXD_CASE(K)                                                                                             \
   case K:                                                                                                     \
-    hipLaunchKernelGGL((k_mdot<VT, K>), dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, basis, v, n, h->partial);      \
+    if constexpr (K > 0)                                                                                      \
+      hipLaunchKernelGGL((k_mdot<VT, K>), dim3(G), dim3(QXD_BLOCK), 0, s, basis, v, n, h->partial);           \
+    break;
+    QXD_K_CASES(QXD_CASE)
+#undef QXD_CASE
+  }
+  launch_final_sum(h->partial, G, 2 * k, G, slots, s, host);
+}
+template <class VT>
+void blas_gcr_update(qxd_handle* h, VT* v, const Ptrs& basis, VT* z, const Ptrs& zbasis, int k, const double* coef,
+                     const VT* r, size_t n, double* slots, hipStream_t s, double* host) {
+  const int G = nred(n);
+  auto go = [&](auto kc) {
+    constexpr int K = decltype(kc)::value;
+    if (z) {
+      // the coarse solver's vectors are float4 pairs
+      if constexpr (std::is_same_v<VT, float4>)
+        hipLaunchKernelGGL((k_gcr_update<VT, K, true>), dim3(G), dim3(QXD_BLOCK), 0, s, v, basis, z, zbasis, coef, r,
+                           n, h->partial);
+    } else {
+      hipLaunchKernelGGL((k_gcr_update<VT, K, false>), dim3(G), dim3(QXD_BLOCK), 0, s, v, basis, z, zbasis, coef, r, n,
+                         h->partial);
+    }
+  };
+  switch (k) {
+#define QXD_CASE(K)                           \
+  case K:                                   \
+    go(std::integral_constant<int, K>{});   \
     break;
     QXD_K_CASES(QXD_CASE)
 #undef QXD_CASE
     default: return;  // callers keep 0 <= k <= QXD_MAXKV
   }
-  launch_final_sum(h->partial, QXD_NRED, 2 * k, QXD_NRED, slots, s);
+  launch_final_sum(h->partial, G, 3, G, slots, s, host);
 }
 template <class VT>
-void blas_mupdate(qxd_handle* h, VT* v, const Ptrs& basis, int k, const double* coef, size_t n, double* slot,
-                  hipStream_t s) {
-  switch (k) {
-#define QXD_CASE(K)                                                                                             \
-  case K:                                                                                                     \
-    hipLaunchKernelGGL((k_mupdate<VT, K>), dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, v, basis, coef, n,           \
-                       h->partial);                                                                           \
-    break;
-    QXD_K_CASES(QXD_CASE)
-#undef QXD_CASE
-    default: return;
-  }
-  launch_final_sum(h->partial, QXD_NRED, 1, QXD_NRED, slot, s);
-}
-template <class VT>
-void blas_scale_cdot(qxd_handle* h, VT* v, const VT* r, size_t n, int i_n2, double* slots, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale_cdot<VT>, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, v, r, n, h->scal, i_n2, h->partial);
-  launch_final_sum(h->partial, QXD_NRED, 2, QXD_NRED, slots, s);
-}
-template <class VT>
-void blas_r_update(qxd_handle* h, VT* r, const VT* v, size_t n, int i_c, double* slot, hipStream_t s, VT* r_copy) {
-  hipLaunchKernelGGL(k_r_update<VT>, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, r, v, n, h->scal, i_c, h->partial,
-                     r_copy);
-  launch_final_sum(h->partial, QXD_NRED, 1, QXD_NRED, slot, s);
+void blas_gcr_step(qxd_handle* h, VT* v, VT* r, size_t n, const double* dots, double* slot, hipStream_t s, double* host,
+                   VT* r_copy, VT* z, VT* x) {
+  hipLaunchKernelGGL(k_gcr_step<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, v, r, n, dots, h->partial, r_copy, z, x);
+  if (slot) launch_final_sum(h->partial, nred(n), 1, nred(n), slot, s, host);
 }
 template <class VT>
 void blas_multi_axpy(qxd_handle* h, VT* x, const Ptrs& basis, int k, const double* coef, size_t n, hipStream_t s) {
@@ -431,7 +492,7 @@ void blas_multi_axpy(qxd_handle* h, VT* x, const Ptrs& basis, int k, const doubl
   switch (k) {
 #define QXD_CASE(K)                                                                                             \
   case K:                                                                                                     \
-    hipLaunchKernelGGL((k_multi_axpy<VT, K>), dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, x, basis, coef, n);      \
+    hipLaunchKernelGGL((k_multi_axpy<VT, K>), dim3(nred(n)), dim3(QXD_BLOCK), 0, s, x, basis, coef, n);       \
     break;
     QXD_K_CASES(QXD_CASE)
 #undef QXD_CASE
@@ -440,13 +501,13 @@ void blas_multi_axpy(qxd_handle* h, VT* x, const Ptrs& basis, int k, const doubl
 }
 template <class VT>
 void blas_zero(VT* x, size_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_zero<VT>, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, x, n);
+  hipLaunchKernelGGL(k_zero<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, x, n);
 }
 void blas_down(qxd_handle* h, float4* d, const double2* src, int i_n2, hipStream_t s) {
-  hipLaunchKernelGGL(k_down, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, d, src, (size_t)h->Ve, h->scal, i_n2);
+  hipLaunchKernelGGL(k_down, dim3(nred(6 * (size_t)h->Ve)), dim3(QXD_BLOCK), 0, s, d, src, (size_t)h->Ve, h->scal, i_n2);
 }
 void blas_up_acc(qxd_handle* h, double2* x, const float4* e, int i_n2, hipStream_t s) {
-  hipLaunchKernelGGL(k_up_acc, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, x, e, (size_t)h->Ve, h->scal, i_n2);
+  hipLaunchKernelGGL(k_up_acc, dim3(nred(6 * (size_t)h->Ve)), dim3(QXD_BLOCK), 0, s, x, e, (size_t)h->Ve, h->scal, i_n2);
 }
 
 #define INST(VT)                                                                                        \
@@ -456,11 +517,12 @@ void blas_up_acc(qxd_handle* h, double2* x, const float4* e, int i_n2, hipStream
                                hipStream_t);                                                            \
   template void blas_cg_p<VT>(qxd_handle*, VT*, const VT*, size_t, int, int, hipStream_t);              \
   template void blas_sub_norm<VT>(qxd_handle*, VT*, const VT*, const VT*, size_t, double*, hipStream_t); \
-  template void blas_mdot<VT>(qxd_handle*, const Ptrs&, int, const VT*, size_t, double*, hipStream_t);  \
-  template void blas_mupdate<VT>(qxd_handle*, VT*, const Ptrs&, int, const double*, size_t, double*,    \
-                                 hipStream_t);                                                          \
-  template void blas_scale_cdot<VT>(qxd_handle*, VT*, const VT*, size_t, int, double*, hipStream_t);    \
-  template void blas_r_update<VT>(qxd_handle*, VT*, const VT*, size_t, int, double*, hipStream_t, VT*); \
+  template void blas_mdot<VT>(qxd_handle*, const Ptrs&, int, const VT*, size_t, double*, hipStream_t,   \
+                              double*);                                                                 \
+  template void blas_gcr_update<VT>(qxd_handle*, VT*, const Ptrs&, VT*, const Ptrs&, int, const double*, \
+                                    const VT*, size_t, double*, hipStream_t, double*);                  \
+  template void blas_gcr_step<VT>(qxd_handle*, VT*, VT*, size_t, const double*, double*, hipStream_t,   \
+                                  double*, VT*, VT*, VT*);                                              \
   template void blas_multi_axpy<VT>(qxd_handle*, VT*, const Ptrs&, int, const double*, size_t,          \
                                     hipStream_t);                                                       \
   template void blas_zero<VT>(VT*, size_t, hipStream_t);

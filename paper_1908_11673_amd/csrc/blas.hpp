@@ -18,17 +18,20 @@ void blas_cg_xr(qxd_handle* h, VT* x, VT* r, const VT* p, const VT* w, size_t n,
 template <class VT> void blas_cg_p(qxd_handle* h, VT* p, const VT* z, size_t n, int i_new, int i_old, hipStream_t s);
 template <class VT>
 void blas_sub_norm(qxd_handle* h, VT* r, const VT* b, const VT* w, size_t n, double* slot, hipStream_t s);
+// host (below): pinned memory that the sums are written to as well, or null
 template <class VT>
-void blas_mdot(qxd_handle* h, const Ptrs& basis, int k, const VT* v, size_t n, double* slots, hipStream_t s);
+void blas_mdot(qxd_handle* h, const Ptrs& basis, int k, const VT* v, size_t n, double* slots, hipStream_t s,
+               double* host = nullptr);
+// v -= sum_j c_j basis_j and, unless z is null (float4 only), z -= sum_j c_j zbasis_j;
+// slots: |v|^2 and (v, r)
 template <class VT>
-void blas_mupdate(qxd_handle* h, VT* v, const Ptrs& basis, int k, const double* coef, size_t n, double* slot,
-                  hipStream_t s);
+void blas_gcr_update(qxd_handle* h, VT* v, const Ptrs& basis, VT* z, const Ptrs& zbasis, int k, const double* coef,
+                     const VT* r, size_t n, double* slots, hipStream_t s, double* host = nullptr);
+// from dots = |v|^2, (v, r): v /= |v|, r -= (v, r) v (also to r_copy), slot = |r|^2;
+// unless z is null z /= |v|, x += (v, r) z
 template <class VT>
-void blas_scale_cdot(qxd_handle* h, VT* v, const VT* r, size_t n, int i_n2, double* slots, hipStream_t s);
-// r -= c v; with r_copy the new r is written there too
-template <class VT>
-void blas_r_update(qxd_handle* h, VT* r, const VT* v, size_t n, int i_c, double* slot, hipStream_t s,
-                   VT* r_copy = nullptr);
+void blas_gcr_step(qxd_handle* h, VT* v, VT* r, size_t n, const double* dots, double* slot, hipStream_t s,
+                   double* host = nullptr, VT* r_copy = nullptr, VT* z = nullptr, VT* x = nullptr);
 template <class VT>
 void blas_multi_axpy(qxd_handle* h, VT* x, const Ptrs& basis, int k, const double* coef, size_t n, hipStream_t s);
 template <class VT> void blas_zero(VT* x, size_t n, hipStream_t s);

@@ -49,7 +49,7 @@ constexpr int kDflMaxNs = QXD_DFL_MAXNS;
 constexpr int kDflMaxNc = QXD_DFL_MAXNC;
 
 // device scalar slots (after the multi-shift solver's)
-enum { S_DC = 3880, S_DN = S_DC + 2 * kDflMaxNc, S_DA = S_DN + 2, S_DX = S_DA + 2, S_DY = S_DX + 2, S_DEND = S_DY + 2 };
+enum { S_DC = 3880, S_DD = S_DC + 2 * kDflMaxNc, S_DY = S_DD + 3, S_DEND = S_DY + 1 };
 static_assert(S_DEND <= QXD_NSCAL - 8, "scalar slots");
 
 __device__ __forceinline__ void dfl_site(const Geo& g, const SapGeo& sb, int B, int t, int& x0, int& x1, int& x2,
@@ -351,25 +351,46 @@ __global__ __launch_bounds__(kSapSites) void k_dfl_prolong(Geo g, SapGeo sb, int
   sp_store(p ? out_o : out_e, g.Ve, h, o);
 }
 
-// y = A x (one thread per coarse row); z = x when given
-__global__ __launch_bounds__(QXD_BLOCK) void k_dfl_cmv(int nblk, int ns, const float2* __restrict__ A,
-                                                       const int* __restrict__ nbr, const float2* __restrict__ x,
-                                                       float2* __restrict__ y, float2* __restrict__ z) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (size_t)nblk * ns) return;
-  const int B = (int)(i / ns), l = (int)(i % ns);
+// y = A x, z = x.  One wavefront per block: its lanes are 64 / ns groups of ns
+// rows, the 9 ns columns of the block's row of A going to the groups in turn
+// (consecutive lanes read consecutive words), with the nine blocks of x in LDS.
+// HBM bound on large lattices (A is read once); at 32 x 16^3 (1024 blocks, ns 16)
+// one work-item per row left three quarters of the chip idle behind 144 loads in
+// a row: 24 -> 6 us.
+constexpr int kCmvWaves = 4;
+__global__ __launch_bounds__(64 * kCmvWaves) void k_dfl_cmv(int nblk, int ns, const float2* __restrict__ A,
+                                                            const int* __restrict__ nbr, const float2* __restrict__ x,
+                                                            float2* __restrict__ y, float2* __restrict__ z) {
+  __shared__ float2 xs[kCmvWaves][9 * kDflMaxNs];
+  __shared__ float2 red[kCmvWaves][64];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int B = blockIdx.x * kCmvWaves + w;
+  const bool in = B < nblk;
+  const int nc = 9 * ns, groups = 64 / ns, gr = lane / ns, l = lane % ns;
+  if (in)
+    for (int c = lane; c < nc; c += 64) xs[w][c] = x[(size_t)nbr[(size_t)9 * B + c / ns] * ns + c % ns];
+  __syncthreads();
   float re = 0.f, im = 0.f;
-  for (int n = 0; n < 9; ++n) {
-    const float2* a = A + ((size_t)B * 9 + n) * ns * ns + l;
-    const float2* xv = x + (size_t)nbr[(size_t)9 * B + n] * ns;
-    for (int k = 0; k < ns; ++k) {
-      const float2 av = a[(size_t)k * ns], xk = xv[k];
+  if (in && gr < groups) {
+    const float2* a = A + (size_t)B * nc * ns + l;
+#pragma unroll 12
+    for (int c = gr; c < nc; c += groups) {
+      const float2 av = a[(size_t)c * ns], xk = xs[w][c];
       re += av.x * xk.x - av.y * xk.y;
       im += av.x * xk.y + av.y * xk.x;
     }
   }
+  red[w][lane] = make_float2(re, im);
+  __syncthreads();
+  if (!in || lane >= ns) return;
+  for (int q = 1; q < groups; ++q) {
+    const float2 v = red[w][q * ns + lane];
+    re += v.x;
+    im += v.y;
+  }
+  const size_t i = (size_t)B * ns + lane;
   y[i] = make_float2(re, im);
-  if (z) z[i] = x[i];
+  z[i] = xs[w][lane];
 }
 
 // t_e = r_e - t_e, t_o = -t_o (t holds D psi on entry)
@@ -416,34 +437,23 @@ int dfl_grid(size_t n) { return (int)std::min<size_t>(QXD_NRED, (n + QXD_BLOCK -
 
 // nc GCR steps on A c = b from c = 0, no restart; every scalar stays on the
 // device.  The coarse vectors are viewed as float4 pairs of complex numbers.
+// Bound by launches (six a step, of 3 to 6 us at 32 x 16^3).
 qxd_status dfl_coarse(qxd_handle* h, qxd_dfl* d, int nc, hipStream_t s) {
   const size_t N = (size_t)d->nblk * d->ns, n4 = N / 2;
   auto v4 = [](float2* p) { return reinterpret_cast<float4*>(p); };
   blas_zero<float4>(v4(d->cx), n4, s);
   QXD_HIP(hipMemcpyAsync(d->cr, d->cb, N * sizeof(float2), hipMemcpyDeviceToDevice, s));
-  const int g = (int)((N + QXD_BLOCK - 1) / QXD_BLOCK);
+  Ptrs pw{}, pz{};
   for (int k = 0; k < nc; ++k) {
     float2* z = d->cz + k * N;
     float2* w = d->cw + k * N;
-    hipLaunchKernelGGL(k_dfl_cmv, dim3(g), dim3(QXD_BLOCK), 0, s, d->nblk, d->ns, d->A, d->nbr, d->cr, w, z);
-    if (k == 0) {
-      blas_norm2<float4>(h, v4(w), n4, h->scal + S_DN, s);
-    } else {
-      Ptrs pw{}, pz{};
-      for (int j = 0; j < k; ++j) {
-        pw.p[j] = d->cw + j * N;
-        pz.p[j] = d->cz + j * N;
-      }
-      blas_mdot<float4>(h, pw, k, v4(w), n4, h->scal + S_DC, s);
-      blas_mupdate<float4>(h, v4(w), pw, k, h->scal + S_DC, n4, h->scal + S_DN, s);
-      blas_mupdate<float4>(h, v4(z), pz, k, h->scal + S_DC, n4, h->scal + S_DY, s);
-    }
-    blas_scale_cdot<float4>(h, v4(w), v4(d->cr), n4, S_DN, h->scal + S_DA, s);
-    blas_scale_cdot<float4>(h, v4(z), v4(d->cr), n4, S_DN, h->scal + S_DX, s);
-    blas_r_update<float4>(h, v4(d->cr), v4(w), n4, S_DA, h->scal + S_DY, s);
-    Ptrs pz1{};
-    pz1.p[0] = z;
-    blas_multi_axpy<float4>(h, v4(d->cx), pz1, 1, h->scal + S_DA, n4, s);
+    hipLaunchKernelGGL(k_dfl_cmv, dim3((d->nblk + kCmvWaves - 1) / kCmvWaves), dim3(64 * kCmvWaves), 0, s, d->nblk,
+                       d->ns, d->A, d->nbr, d->cr, w, z);
+    blas_mdot<float4>(h, pw, k, v4(w), n4, h->scal + S_DC, s);
+    blas_gcr_update<float4>(h, v4(w), pw, v4(z), pz, k, h->scal + S_DC, v4(d->cr), n4, h->scal + S_DD, s);
+    blas_gcr_step<float4>(h, v4(w), v4(d->cr), n4, h->scal + S_DD, nullptr, s, nullptr, nullptr, v4(z), v4(d->cx));
+    pw.p[k] = w;
+    pz.p[k] = z;
   }
   QXD_HIP(hipGetLastError());
   return QXD_OK;

@@ -394,6 +394,7 @@ struct qxd_handle {
   // solver workspaces (grow-only), indexed by role
   void* ws[64] = {};
   size_t ws_bytes[64] = {};
+  hipEvent_t step_done = nullptr;  // FGCR: the scalars of a step are on the host
 };
 
 #define QXD_NSCAL 4096
@@ -403,8 +404,7 @@ struct qxd_handle {
 enum {
   S_ZZ0 = 0, S_ZZ1 = 1, S_WW = 2, S_RR = 3, S_NB = 4, S_RT = 5, S_BH = 6, S_ONE = 7,
   S_FRR = 16,            // FGCR |r|^2
-  S_FB = 32,             // FGCR |chi_k|^2, k < 64
-  S_FC = 128,            // FGCR c_k (complex), k < 64
+  S_FB = 32,             // FGCR |chi_k|^2 and (chi_k, r) (complex), before chi_k is normalised: 3 slots each
   S_FR = 1024,           // FGCR R[k][j] (complex), column k at S_FR + 2 k QXD_MAXKV_R
   S_FAL = 3200,          // FGCR solution coefficients (complex)
   S_NN = 3400            // network preconditioner scratch scalars
@@ -455,7 +455,9 @@ inline int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 // internal entry points shared between translation units
 // out[v] = sum_{i<n} partial[v * stride + i] for v < nvals, summed in a fixed order
-void launch_final_sum(const double* partial, int n, int nvals, int stride, double* out, hipStream_t s);
+// (host: pinned memory that they are written to as well, or null)
+void launch_final_sum(const double* partial, int n, int nvals, int stride, double* out, hipStream_t s,
+                      double* host = nullptr);
 qxd_status qxd_schur_apply(qxd_handle* h, qxd_prec p, int dagger, void* out_e, const void* in_e, double* norm_slot,
                            hipStream_t s);
 qxd_status nn_apply_internal(qxd_handle* h, qxd_nn* net, float4* out_e, const float4* in_e, hipStream_t s);

@@ -78,14 +78,7 @@ struct InnerOp {
 };
 
 template <class VT>
-qxd_status apply_op(qxd_handle* h, InnerOp op, VT* out, const VT* in, double* norm_slot, hipStream_t s) {
-  if (op.mode == 0) return qxd_schur_apply(h, QXD_F64, 0, out, in, norm_slot, s);
-  if (op.mode == 1) return qxd_schur_apply(h, QXD_F32, 0, out, in, norm_slot, s);
-  return qxd_schur_apply_mixed(h, 0, (float4*)out, (const float4*)in, norm_slot, s);
-}
-
-template <class VT>
-qxd_status apply_op_dag(qxd_handle* h, InnerOp op, int dagger, VT* out, const VT* in, double* norm_slot,
+qxd_status apply_op(qxd_handle* h, InnerOp op, int dagger, VT* out, const VT* in, double* norm_slot,
                         hipStream_t s) {
   if (op.mode == 0) return qxd_schur_apply(h, QXD_F64, dagger, out, in, norm_slot, s);
   if (op.mode == 1) return qxd_schur_apply(h, QXD_F32, dagger, out, in, norm_slot, s);
@@ -101,15 +94,15 @@ qxd_status cgnr(qxd_handle* h, InnerOp op, VT* x, VT* r, VT* p, VT* z, VT* w, si
                 int max_steps, int check, int* steps, int64_t* applies, hipStream_t s) {
   const size_t bytes = n * sizeof(VT);
   blas_zero<VT>(x, n, s);
-  QXD_TRY(apply_op_dag<VT>(h, op, 1, z, r, h->scal + S_ZZ0, s));
+  QXD_TRY(apply_op<VT>(h, op, 1, z, r, h->scal + S_ZZ0, s));
   QXD_HIP(hipMemcpyAsync(p, z, bytes, hipMemcpyDeviceToDevice, s));
   *applies += 1;
   int it = 0;
   while (it < max_steps) {
     const int zo = S_ZZ0 + (it & 1), zn = S_ZZ0 + ((it + 1) & 1);
-    QXD_TRY(apply_op_dag<VT>(h, op, 0, w, p, h->scal + S_WW, s));
+    QXD_TRY(apply_op<VT>(h, op, 0, w, p, h->scal + S_WW, s));
     blas_cg_xr<VT>(h, x, r, p, w, n, zo, S_WW, S_FRR, s);
-    QXD_TRY(apply_op_dag<VT>(h, op, 1, z, r, h->scal + zn, s));
+    QXD_TRY(apply_op<VT>(h, op, 1, z, r, h->scal + zn, s));
     blas_cg_p<VT>(h, p, z, n, zn, zo, s);
     *applies += 2;
     ++it;
@@ -158,12 +151,18 @@ struct FgcrResult {
 // Flexible GCR on op x = b, x starting at zero; r holds b on entry and the
 // recursive residual on exit.  Classical Gram-Schmidt of chi_k against the
 // previous directions, normalisation, then r -= (chi_k, r) chi_k; at the end of
-// each cycle x += Phi alpha with R alpha = c solved on the host in FP64.  The
-// host waits once per step, for |chi_k|^2 and |r|^2 together: a direction whose
-// norm is zero or not finite is zeroed by the normalisation, so the residual
-// update leaves r as it was and the step can be redone without the
-// preconditioner.  Without a preconditioner phi_k = r_k, and the residual
-// update of step k writes r_{k+1} to phi_{k+1} as well (phi_0 is a copy).
+// each cycle x += Phi alpha with R alpha = c solved on the host in FP64.
+//
+// A step after the operator is a multi-dot, one pass that orthogonalises chi_k
+// and takes |chi_k|^2 and (chi_k, r), and one that normalises it and updates r;
+// the final sums also write their values to the host's pinned mirror, so that
+// the host waits for an event and copies nothing.  Without a preconditioner
+// phi_k = r_k: the residual update of step k writes r_{k+1} to phi_{k+1} as well
+// (phi_0 is a copy), and the operator of step k + 1 is queued before the host
+// waits, so that the GPU works on while it does (one application in vain at the
+// end of a solve).  A direction whose norm is zero or not finite is zeroed by
+// the normalisation, so the residual update leaves r as it was and the step can
+// be redone without the preconditioner.  32 x 16^3, FP32: 165 -> 128 us a step.
 template <class VT>
 qxd_status fgcr(qxd_handle* h, InnerOp op, Precond pc, int fallback_after, VT* x, VT* r, size_t n, int nkv,
                 double tol_abs, int max_steps, FgcrResult* res, hipStream_t s,
@@ -175,18 +174,20 @@ qxd_status fgcr(qxd_handle* h, InnerOp op, Precond pc, int fallback_after, VT* x
     chi[k] = (VT*)ws_get(h, W_CHI + k, bytes);
     if (!phi[k] || !chi[k]) return QXD_ENOMEM;
   }
+  if (!h->step_done) QXD_HIP(hipEventCreateWithFlags(&h->step_done, hipEventDisableTiming));
+  double* const hs = h->scal_host;
   blas_zero<VT>(x, n, s);
   blas_norm2<VT>(h, r, n, h->scal + S_FRR, s);
   QXD_TRY(read_scal(h, S_FRR, 1, s));
-  double rr = h->scal_host[S_FRR];
+  double rr = hs[S_FRR];
   if (!std::isfinite(rr)) return QXD_ENAN;
   bool use_nn = pc.any();
-  bool r_in_phi = false;  // phi[k] already holds r (written by the previous residual update)
   double best = std::sqrt(rr);
   int since_best = 0;
   int steps = 0;
   while (std::sqrt(rr) > tol_abs && steps < max_steps) {
     int m = 0;
+    bool ahead = false;  // phi[k] holds r and chi[k] its image already
     for (int k = 0; k < nkv && steps < max_steps; ++k) {
       bool redo = true;
       while (redo) {
@@ -197,31 +198,27 @@ qxd_status fgcr(qxd_handle* h, InnerOp op, Precond pc, int fallback_after, VT* x
             res->nn_applies++;
           else
             res->sap_applies++;
-        } else if (k == 0 || !r_in_phi) {
+        } else if (!ahead) {
           QXD_HIP(hipMemcpyAsync(phi[k], r, bytes, hipMemcpyDeviceToDevice, s));
         }
-        if (k == 0) {
-          QXD_TRY(apply_op<VT>(h, op, chi[k], phi[k], h->scal + S_FB + k, s));
-        } else {
-          QXD_TRY(apply_op<VT>(h, op, chi[k], phi[k], nullptr, s));
-          Ptrs bp{};
-          for (int j = 0; j < k; ++j) bp.p[j] = chi[j];
-          double* col = h->scal + S_FR + 2 * k * QXD_MAXKV_R;
-          blas_mdot<VT>(h, bp, k, chi[k], n, col, s);
-          blas_mupdate<VT>(h, chi[k], bp, k, col, n, h->scal + S_FB + k, s);
-        }
+        if (!ahead) QXD_TRY(apply_op<VT>(h, op, 0, chi[k], phi[k], nullptr, s));
+        Ptrs bp{};
+        for (int j = 0; j < k; ++j) bp.p[j] = chi[j];
+        const int col = S_FR + 2 * k * QXD_MAXKV_R, dots = S_FB + 3 * k;
+        blas_mdot<VT>(h, bp, k, chi[k], n, h->scal + col, s, hs + col);
+        blas_gcr_update<VT>(h, chi[k], bp, nullptr, bp, k, h->scal + col, r, n, h->scal + dots, s, hs + dots);
         res->applies++;
-        blas_scale_cdot<VT>(h, chi[k], r, n, S_FB + k, h->scal + S_FC + 2 * k, s);
         // plain FGCR: the next step's phi is the new residual
-        r_in_phi = !use_nn && k + 1 < nkv;
-        blas_r_update<VT>(h, r, chi[k], n, S_FC + 2 * k, h->scal + S_FRR, s, r_in_phi ? phi[k + 1] : nullptr);
-        QXD_HIP(hipMemcpyAsync(h->scal_host + S_FB + k, h->scal + S_FB + k, sizeof(double), hipMemcpyDeviceToHost,
-                               s));
-        QXD_TRY(read_scal(h, S_FRR, 1, s));
-        double b2 = h->scal_host[S_FB + k];
+        ahead = !use_nn && k + 1 < nkv && steps + 1 < max_steps;
+        blas_gcr_step<VT>(h, chi[k], r, n, h->scal + dots, h->scal + S_FRR, s, hs + S_FRR,
+                          ahead ? phi[k + 1] : nullptr);
+        QXD_HIP(hipEventRecord(h->step_done, s));
+        if (ahead) QXD_TRY(apply_op<VT>(h, op, 0, chi[k + 1], phi[k + 1], nullptr, s));
+        QXD_HIP(hipEventSynchronize(h->step_done));
+        double b2 = hs[dots];
         if (!std::isfinite(b2) || !(b2 > 0.0)) {
           // chi_k was zeroed and r is unchanged
-          r_in_phi = false;
+          ahead = false;
           if (use_nn) {  // the preconditioner produced a useless direction: drop it, redo the step plainly
             use_nn = false;
             res->fell_back = true;
@@ -231,7 +228,7 @@ qxd_status fgcr(qxd_handle* h, InnerOp op, Precond pc, int fallback_after, VT* x
           return std::isfinite(b2) ? QXD_ENOCONV : QXD_ENAN;
         }
       }
-      rr = h->scal_host[S_FRR];
+      rr = hs[S_FRR];
       ++m;
       ++steps;
       if (!std::isfinite(rr)) return QXD_ENAN;
@@ -245,25 +242,22 @@ qxd_status fgcr(qxd_handle* h, InnerOp op, Precond pc, int fallback_after, VT* x
       }
       if (rn <= tol_abs) break;
     }
-    // x += sum_k alpha_k phi_k with R alpha = c
-    QXD_TRY(read_scal(h, S_FB, m, s));
-    QXD_TRY(read_scal(h, S_FC, 2 * m, s));
-    QXD_TRY(read_scal(h, S_FR, 2 * m * QXD_MAXKV_R, s));
+    // x += sum_k alpha_k phi_k with R alpha = c, c_k = (chi_k, r) / |chi_k|
     std::vector<std::complex<double>> al(m);
     for (int k = m - 1; k >= 0; --k) {
-      std::complex<double> v(h->scal_host[S_FC + 2 * k], h->scal_host[S_FC + 2 * k + 1]);
-      for (int j = k + 1; j < m; ++j) {
-        std::complex<double> a(h->scal_host[S_FR + 2 * (j * QXD_MAXKV_R + k)],
-                               h->scal_host[S_FR + 2 * (j * QXD_MAXKV_R + k) + 1]);
-        v -= a * al[j];
-      }
-      al[k] = v / std::sqrt(h->scal_host[S_FB + k]);
+      const double n2 = hs[S_FB + 3 * k];
+      std::complex<double> v(hs[S_FB + 3 * k + 1], hs[S_FB + 3 * k + 2]);
+      v /= std::sqrt(n2);
+      for (int j = k + 1; j < m; ++j)
+        v -= std::complex<double>(hs[S_FR + 2 * (j * QXD_MAXKV_R + k)], hs[S_FR + 2 * (j * QXD_MAXKV_R + k) + 1]) * al[j];
+      al[k] = v / std::sqrt(n2);
     }
+    // (the copy of an earlier cycle out of these slots has ended: steps were waited for since)
     for (int k = 0; k < m; ++k) {
-      h->scal_host[S_FAL + 2 * k] = al[k].real();
-      h->scal_host[S_FAL + 2 * k + 1] = al[k].imag();
+      hs[S_FAL + 2 * k] = al[k].real();
+      hs[S_FAL + 2 * k + 1] = al[k].imag();
     }
-    QXD_HIP(hipMemcpyAsync(h->scal + S_FAL, h->scal_host + S_FAL, 2 * m * sizeof(double), hipMemcpyHostToDevice, s));
+    QXD_HIP(hipMemcpyAsync(h->scal + S_FAL, hs + S_FAL, 2 * m * sizeof(double), hipMemcpyHostToDevice, s));
     Ptrs pp{};
     for (int j = 0; j < m; ++j) pp.p[j] = phi[j];
     blas_multi_axpy<VT>(h, x, pp, m, h->scal + S_FAL, n, s);
