@@ -282,6 +282,7 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_gcr_update(VT* __restrict__ v, Pt
           bj[j] = ld_stream(&((const VT*)basis.p[j0 + j])[i]);
           if (Z) zj[j] = ld_stream(&((const VT*)zbasis.p[j0 + j])[i]);
         }
+      if (Z) __builtin_amdgcn_sched_barrier(0);  // else the loads are issued one by one, each next to its use
 #pragma unroll
       for (int j = 0; j < QXD_KGROUP; ++j)
         if (j0 + j < K) {
