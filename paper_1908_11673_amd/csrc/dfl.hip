@@ -287,18 +287,20 @@ __global__ __launch_bounds__(kSapSites) void k_dfl_little(Geo g, SapGeo sb, int 
         U[mu][c] = mk(v.x, v.y);
       }
   }
+  sap_lds_init(L);
   const float4* cb = sap_blk<18>(Cb, B) + t;
   const size_t bsz = (size_t)ns * 6 * kSapSites;
   const float4* wb = W + (size_t)B * bsz;
   for (int k = 0; k < ns; ++k) {
     cx<float> w[12], acc[12], v[12];
     sp_load(wb + (size_t)k * 6 * kSapSites, kSapSites, t, w);
-    sap_publish<false>(L, w, U);
+    sap_publish<false>(L, t, w, U);
     __syncthreads();
-    sap_gather<false>(L, U, acc);
-    sap_clover<kSapSites>(cb, w, v);
+    sap_zero(acc);
+    sap_gather<false>(L, t, U, acc);
+    sap_clover<kSapSites>(cb, w, v);  // -2 H w
 #pragma unroll
-    for (int c = 0; c < 12; ++c) v[c] = v[c] - 0.5f * acc[c];
+    for (int c = 0; c < 12; ++c) v[c] = -0.5f * (v[c] + acc[c]);
     // (the projections' barriers also separate these reads from the next publish)
     dfl_project<false>(red, wb + t, v, ns, A + ((size_t)B * 9 * ns + k) * ns, 1);
     dfl_faces<0>(g, sb, red, B, x0, x1, x2, x3, l0, w, U[0], W, Vb, nbr, ns, k, A);

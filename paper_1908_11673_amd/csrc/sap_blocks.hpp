@@ -2,6 +2,8 @@
 // block geometry and block order, and the in-block hop exchange through LDS
 // (see sap.hip for the method and the layout).
 #pragma once
+#include <type_traits>
+
 #include "wilson_site.hpp"
 
 struct SapGeo {
@@ -13,6 +15,9 @@ namespace {
 
 constexpr int kSapB = 4;                            // block extent
 constexpr int kSapSites = kSapB * kSapB * kSapB * kSapB;  // 256: one thread per site
+// slots of the exchange buffers: a site each, then one that holds zeros, which
+// hops that leave the block read, so that no hop needs a branch
+constexpr int kSapZero = kSapSites, kSapSlots = kSapSites + 4;
 
 
 // Slot of the site with local index s and its inverse: parity-sorted for the
@@ -141,30 +146,35 @@ __device__ __forceinline__ void sap_herm6(const float* b, const cx<float>* in, c
   }
 }
 
-// Plain (cached) loads: every step of a block solve reads the clover blocks
-// again.  cb points at the site's first component, components STRIDE apart.
+// One 6 x 6 block of a site (36 registers), HALF its chirality.  Plain (cached)
+// loads: every step of a block solve reads the clover blocks again.  cb points
+// at the site's first component, components STRIDE apart.
+template <int STRIDE, int HALF>
+__device__ __forceinline__ void sap_clover_load(const float4* __restrict__ cb, float r[36]) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const float4 v = cb[(9 * HALF + k) * STRIDE];
+    r[4 * k] = v.x;
+    r[4 * k + 1] = v.y;
+    r[4 * k + 2] = v.z;
+    r[4 * k + 3] = v.w;
+  }
+}
+
 template <int STRIDE>
 __device__ __forceinline__ void sap_clover(const float4* __restrict__ cb, const cx<float> in[12],
                                            cx<float> out[12]) {
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {  // one 6 x 6 block at a time: 36 registers of clover
-    float r[36];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      float4 v = cb[(9 * half + k) * STRIDE];
-      r[4 * k] = v.x;
-      r[4 * k + 1] = v.y;
-      r[4 * k + 2] = v.z;
-      r[4 * k + 3] = v.w;
-    }
-    sap_herm6(r, in + 6 * half, out + 6 * half);
-  }
+  float r[36];
+  sap_clover_load<STRIDE, 0>(cb, r);
+  sap_herm6(r, in, out);
+  sap_clover_load<STRIDE, 1>(cb, r);
+  sap_herm6(r, in + 6, out + 6);
 }
 
 // The backward hop that site t contributes to its forward neighbour along MU:
 // (1 + g_MU) U(t, MU)^+ rho(t), kept as the two multiplied colour vectors.
 template <int MU>
-__device__ __forceinline__ void sap_send(float2 (*bw_s)[6][kSapSites], int t, const cx<float> rho[12],
+__device__ __forceinline__ void sap_send(float2 (*bw_s)[6][kSapSlots], int t, const cx<float> rho[12],
                                          const cx<float> u[9]) {
   cx<float> h0[3], h1[3], w0[3], w1[3];
   spin_project<MU, false>(rho, h0, h1);
@@ -181,55 +191,76 @@ __device__ __forceinline__ void sap_send(float2 (*bw_s)[6][kSapSites], int t, co
 // the site's own link and the neighbour's rho, backward as sent by the
 // neighbour.  Neighbours have the other parity: with EO, slot 128 (1 - q) + s' / 2.
 template <int MU, bool EO>
-__device__ __forceinline__ void sap_recv(const float4 (*rho_s)[kSapSites], const float2 (*bw_s)[6][kSapSites], int s,
+__device__ __forceinline__ void sap_recv(const float4 (*rho_s)[kSapSlots], const float2 (*bw_s)[6][kSapSlots], int s,
                                          int q, int l, const cx<float> u[9], cx<float> acc[12]) {
   constexpr int st = MU == 0 ? 64 : MU == 1 ? 16 : MU == 2 ? 4 : 1;
   const int other = EO ? (q ^ 1) << 7 : 0;
-  if (l < kSapB - 1) {
-    const int tn = EO ? other | ((s + st) >> 1) : s + st;
-    cx<float> f[12];
+  const int tf = l < kSapB - 1 ? (EO ? other | ((s + st) >> 1) : s + st) : kSapZero;
+  const int tb = l > 0 ? (EO ? other | ((s - st) >> 1) : s - st) : kSapZero;
+  cx<float> f[12];
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      float4 v = rho_s[j][tn];
-      f[2 * j] = mk(v.x, v.y);
-      f[2 * j + 1] = mk(v.z, v.w);
-    }
-    sap_hop_term<MU, true>(acc, f, u, false);
+  for (int j = 0; j < 6; ++j) {
+    float4 v = rho_s[j][tf];
+    f[2 * j] = mk(v.x, v.y);
+    f[2 * j + 1] = mk(v.z, v.w);
   }
-  if (l > 0) {
-    const int tn = EO ? other | ((s - st) >> 1) : s - st;
-    cx<float> w0[3], w1[3];
+  sap_hop_term<MU, true>(acc, f, u, false);
+  cx<float> w0[3], w1[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      float2 v0 = bw_s[MU][a][tn], v1 = bw_s[MU][3 + a][tn];
-      w0[a] = mk(v0.x, v0.y);
-      w1[a] = mk(v1.x, v1.y);
-    }
-    spin_rebuild_add<MU, false>(acc, w0, w1);
+  for (int a = 0; a < 3; ++a) {
+    float2 v0 = bw_s[MU][a][tb], v1 = bw_s[MU][3 + a][tb];
+    w0[a] = mk(v0.x, v0.y);
+    w1[a] = mk(v1.x, v1.y);
   }
+  spin_rebuild_add<MU, false>(acc, w0, w1);
 }
 
+// Sum over the wavefront, the same in every lane: within rows of 16 lanes by
+// data-parallel-primitive moves (lane ^ 1, lane ^ 2, then the mirror images of 8
+// and of 16 lanes, whose quads and octets already hold equal sums), then the
+// four rows.  No LDS traffic, unlike lane permutes.
 __device__ __forceinline__ float sap_wave_sum(float v) {
+  auto add = [&](auto ctrl) {
+    constexpr int C = decltype(ctrl)::value;
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), C, 0xf, 0xf, true));
+  };
+  add(std::integral_constant<int, 0xB1>{});   // quad_perm [1, 0, 3, 2]
+  add(std::integral_constant<int, 0x4E>{});   // quad_perm [2, 3, 0, 1]
+  add(std::integral_constant<int, 0x141>{});  // row_half_mirror
+  add(std::integral_constant<int, 0x140>{});  // row_mirror
+  const int i = __builtin_bit_cast(int, v);
+  return (__builtin_bit_cast(float, __builtin_amdgcn_readlane(i, 0)) +
+          __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, 16))) +
+         (__builtin_bit_cast(float, __builtin_amdgcn_readlane(i, 32)) +
+          __builtin_bit_cast(float, __builtin_amdgcn_readlane(i, 48)));
+}
+
+__device__ __forceinline__ void sap_zero(cx<float> a[12]) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+  for (int c = 0; c < 12; ++c) a[c] = mk(0.f, 0.f);
 }
 
 struct SapLds {
-  float4 rho[6][kSapSites];
-  float2 bw[4][6][kSapSites];
+  float4 rho[6][kSapSlots];
+  float2 bw[4][6][kSapSlots];
   float red[3][kSapSites / 64];
 };
 
+// The zero slots (before the barrier that precedes the first exchange).
+__device__ __forceinline__ void sap_lds_init(SapLds& L) {
+  if (threadIdx.x < 6) L.rho[threadIdx.x][kSapZero] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (threadIdx.x < 24) L.bw[threadIdx.x / 6][threadIdx.x % 6][kSapZero] = make_float2(0.f, 0.f);
+}
+
 // Where a thread sits in its block: slot t, local index s, parity q, local
-// coordinates l (cheap to recompute from the thread index wherever needed).
+// coordinates l (cheap to recompute from the slot wherever needed).
 struct SapSite {
   int t, s, q, l0, l1, l2, l3;
 };
 template <bool EO>
-__device__ __forceinline__ SapSite sap_site() {
+__device__ __forceinline__ SapSite sap_site(int t) {
   SapSite w;
-  w.t = threadIdx.x;
+  w.t = t;
   sap_local<EO>(w.t, w.l0, w.l1, w.l2, w.l3);
   w.q = (w.l0 + w.l1 + w.l2 + w.l3) & 1;
   w.s = (w.l0 << 6) | (w.l1 << 4) | (w.l2 << 2) | w.l3;
@@ -237,25 +268,23 @@ __device__ __forceinline__ SapSite sap_site() {
 }
 
 // Publish f at the site (slot t) and the backward hops it owes its forward
-// neighbours.
+// neighbours (those of sites on a forward face are read by nobody).
 template <bool EO>
-__device__ __forceinline__ void sap_publish(SapLds& L, const cx<float> f[12], const cx<float> (*U)[9]) {
-  const SapSite w = sap_site<EO>();
+__device__ __forceinline__ void sap_publish(SapLds& L, int t, const cx<float> f[12], const cx<float> (*U)[9]) {
+  const SapSite w = sap_site<EO>(t);
 #pragma unroll
   for (int j = 0; j < 6; ++j)
     L.rho[j][w.t] = make_float4(f[2 * j].re, f[2 * j].im, f[2 * j + 1].re, f[2 * j + 1].im);
-  if (w.l0 < kSapB - 1) sap_send<0>(L.bw, w.t, f, U[0]);
-  if (w.l1 < kSapB - 1) sap_send<1>(L.bw, w.t, f, U[1]);
-  if (w.l2 < kSapB - 1) sap_send<2>(L.bw, w.t, f, U[2]);
-  if (w.l3 < kSapB - 1) sap_send<3>(L.bw, w.t, f, U[3]);
+  sap_send<0>(L.bw, w.t, f, U[0]);
+  sap_send<1>(L.bw, w.t, f, U[1]);
+  sap_send<2>(L.bw, w.t, f, U[2]);
+  sap_send<3>(L.bw, w.t, f, U[3]);
 }
 
-// acc = the in-block hops at the site of what its neighbours published.
+// acc += the in-block hops at the site of what its neighbours published.
 template <bool EO>
-__device__ __forceinline__ void sap_gather(const SapLds& L, const cx<float> (*U)[9], cx<float> acc[12]) {
-  const SapSite w = sap_site<EO>();
-#pragma unroll
-  for (int c = 0; c < 12; ++c) acc[c] = mk(0.f, 0.f);
+__device__ __forceinline__ void sap_gather(const SapLds& L, int t, const cx<float> (*U)[9], cx<float> acc[12]) {
+  const SapSite w = sap_site<EO>(t);
   sap_recv<0, EO>(L.rho, L.bw, w.s, w.q, w.l0, U[0], acc);
   sap_recv<1, EO>(L.rho, L.bw, w.s, w.q, w.l1, U[1], acc);
   sap_recv<2, EO>(L.rho, L.bw, w.s, w.q, w.l2, U[2], acc);
