@@ -133,17 +133,75 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_hop_add(Geo g, int p, const doubl
 // ---------------------------------------------------------------------------
 // The operator with a site's four directions on four wavefronts, for lattices
 // that leave most of the chip idle with one work-item per site.  A workgroup
-// takes 64 sites: wave mu sums both hops along mu, the four sums meet in LDS,
-// and each wave finishes three of a site's twelve components (rows 3 R .. of
-// the block of chirality B).  Such lattices are bound by the serial loads of a
-// wave (FP64: 216 of 16 bytes a lane and pass, 62 here), not by bandwidth:
-// D_hat on 512 even sites 20.0 -> 11.1 us (FP64), 15.9 -> 11.0 (FP32), on 8192
-// 34.6 -> 14.8 and 20.5 -> 11.6, on 32,768 41.8 -> 31.2 and 23.3 -> 19.2.
+// takes 64 sites: wave mu multiplies both hops along mu, the two-spinors meet in
+// LDS, and each wave finishes three of a site's twelve components (rows 3 R ..
+// of the block of chirality B).  Every sum is taken in the order of the kernels
+// above, so the results are theirs bit for bit.
+// Such lattices are bound by the serial loads of a wave (FP64: 216 of 16 bytes a
+// lane and pass, 62 here), not by bandwidth: D_hat on 512 even sites 20.0 ->
+// 10.5 us (FP64), 15.9 -> 11.0 (FP32), on 8192 34.6 -> 14.8 and 20.5 -> 11.6, on
+// 32,768 41.8 -> 31.2 and 23.3 -> 18.9.
 
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// the two-spinors of the hops along mu: forward, backward
 template <class T>
 struct HopSums {
-  cx<T> v[4][12][64];
+  cx<T> w[4][2][6][64];
 };
+
+// components 6 B .. 6 B + 5 of the hop sum at this lane's site
+template <int MU, int B, class T>
+__device__ __forceinline__ void hop4_add(const HopSums<T>& L, int lane, cx<T> a[6]) {
+#pragma unroll
+  for (int dir = 0; dir < 2; ++dir) {
+    cx<T> t[12], w0[3], w1[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      w0[k] = L.w[MU][dir][k][lane];
+      w1[k] = L.w[MU][dir][3 + k][lane];
+    }
+#pragma unroll
+    for (int k = 0; k < 12; ++k) t[k] = k / 6 == B ? a[k % 6] : mk(T(0), T(0));
+    if (dir == 0)
+      spin_rebuild_add<MU, true>(t, w0, w1);
+    else
+      spin_rebuild_add<MU, false>(t, w0, w1);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) a[k] = t[6 * B + k];
+  }
+}
+
+// both hops along MU at the site (see hop_mu), as two-spinors into LDS
+template <int MU, bool G5IN, class T, class SPT, class LKT>
+__device__ __forceinline__ void hop4_mu(const Geo& g, int h, int lane, int x0, int x1, int x2, int x3,
+                                        const SPT* __restrict__ in, const LKT* __restrict__ Vp,
+                                        const LKT* __restrict__ Vq, HopSums<T>& L) {
+  const size_t Ve = g.Ve;
+  bool negf, negb;
+  const int hf = geo_nb<MU, +1>(g, x0, x1, x2, x3, negf);
+  const int hb = geo_nb<MU, -1>(g, x0, x1, x2, x3, negb);
+  cx<T> s[12], u[9], w0[3], w1[3];
+  sp_load(in, Ve, hf, s);
+  if (G5IN) g5_lower(s);
+  lk_load(Vp, Ve, MU, h, u);
+  hop_two_spinor<MU, true>(s, u, negf, w0, w1);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    L.w[MU][0][k][lane] = w0[k];
+    L.w[MU][0][3 + k][lane] = w1[k];
+  }
+  sp_load(in, Ve, hb, s);
+  if (G5IN) g5_lower(s);
+  lk_load(Vq, Ve, MU, hb, u);
+  hop_two_spinor<MU, false>(s, u, negb, w0, w1);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    L.w[MU][1][k][lane] = w0[k];
+    L.w[MU][1][3 + k][lane] = w1[k];
+  }
+}
 
 // components 6 B .. 6 B + 5 of site h
 template <int B, class T, class SPT>
@@ -164,16 +222,23 @@ __device__ __forceinline__ void sp_store_one(uint4* __restrict__ f, size_t Ve, i
   reinterpret_cast<uint32_t*>(f + (c >> 2) * Ve + h)[c & 3] = pack_bf16x2(v.re, v.im);
 }
 
-// row I of a packed block times v
+// row I of a packed Hermitian block times v.  The fused products are those that
+// the compiler makes of herm6_mul in the kernels above, so that both forms of
+// the operator round alike: bfloat16 consumers of its result amplify a last bit.
 template <int I, class T>
 __device__ __forceinline__ cx<T> herm6_row(const T* b, const cx<T> v[6]) {
-  cx<T> o = b[I] * v[I];
+  cx<T> o;
 #pragma unroll
-  for (int j = 0; j < 6; ++j) {
-    if (j == I) continue;
+  for (int n = 0; n < 5; ++n) {
+    const int j = n < I ? n : n + 1;
     const int k = j > I ? herm6_off(I, j) : herm6_off(j, I);
-    const cx<T> hij = mk(b[k], b[k + 1]);
-    o = o + (j > I ? hij * v[j] : cmul_conj(hij, v[j]));
+    const T re = b[k], im = b[k + 1];
+    cx<T> t;
+    if (j > I)
+      t = mk(fma_t(re, v[j].re, -(im * v[j].im)), fma_t(im, v[j].re, re * v[j].im));
+    else
+      t = mk(fma_t(re, v[j].re, im * v[j].im), fma_t(re, v[j].im, -(im * v[j].re)));
+    o = n == 0 ? mk(fma_t(b[I], v[I].re, t.re), fma_t(b[I], v[I].im, t.im)) : o + t;
   }
   return o;
 }
@@ -215,9 +280,14 @@ __device__ __forceinline__ double hop4_finish(const Geo& g, int h, bool in, HopS
   if (BASE) sp_load_half<B, T>(base, Ve, h, s);
   __syncthreads();
 #pragma unroll
-  for (int c = 0; c < 6; ++c) {
-    a[c] = (L.v[0][6 * B + c][lane] + L.v[1][6 * B + c][lane]) + (L.v[2][6 * B + c][lane] + L.v[3][6 * B + c][lane]);
-    if (G5HOP && B == 1) a[c] = -a[c];
+  for (int c = 0; c < 6; ++c) a[c] = mk(T(0), T(0));
+  hop4_add<0, B>(L, lane, a);
+  hop4_add<1, B>(L, lane, a);
+  hop4_add<2, B>(L, lane, a);
+  hop4_add<3, B>(L, lane, a);
+  if (G5HOP && B == 1) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) a[c] = -a[c];
   }
   const cx<T>* v = BASE ? s : a;
   cx<T> o[3] = {herm6_row<3 * R>(r, v), herm6_row<3 * R + 1>(r, v), herm6_row<3 * R + 2>(r, v)};
@@ -250,17 +320,12 @@ __global__ __launch_bounds__(256) void k_hop4(Geo g, int p, const SPT* __restric
   const int h = in ? tile * 64 + lane : g.Ve - 1;  // work-items past the end repeat the last site and store nothing
   int x0, x1, x2, x3;
   geo_decode(g, p, h, x0, x1, x2, x3);
-  cx<T> acc[12];
-#pragma unroll
-  for (int c = 0; c < 12; ++c) acc[c] = mk(T(0), T(0));
   switch (w) {
-    case 0: hop_mu<0, G5IN, T>(g, h, x0, x1, x2, x3, in_q, Vp, Vq, acc); break;
-    case 1: hop_mu<1, G5IN, T>(g, h, x0, x1, x2, x3, in_q, Vp, Vq, acc); break;
-    case 2: hop_mu<2, G5IN, T>(g, h, x0, x1, x2, x3, in_q, Vp, Vq, acc); break;
-    default: hop_mu<3, G5IN, T>(g, h, x0, x1, x2, x3, in_q, Vp, Vq, acc); break;
+    case 0: hop4_mu<0, G5IN>(g, h, lane, x0, x1, x2, x3, in_q, Vp, Vq, L); break;
+    case 1: hop4_mu<1, G5IN>(g, h, lane, x0, x1, x2, x3, in_q, Vp, Vq, L); break;
+    case 2: hop4_mu<2, G5IN>(g, h, lane, x0, x1, x2, x3, in_q, Vp, Vq, L); break;
+    default: hop4_mu<3, G5IN>(g, h, lane, x0, x1, x2, x3, in_q, Vp, Vq, L); break;
   }
-#pragma unroll
-  for (int c = 0; c < 12; ++c) L.v[w][c][lane] = acc[c];
   double n2;
   switch (w) {
     case 0: n2 = hop4_finish<BASE, 0, 0, G5HOP>(g, h, in, L, base, out, C, alpha); break;
@@ -474,18 +539,19 @@ qxd_status qxd_schur_apply(qxd_handle* h, qxd_prec p, int dagger, void* out_e, c
   QXD_TRY(ensure_t(h, p));
   if (p != QXD_F64) QXD_TRY(ensure_copies(h, (p == QXD_F32 ? CP_V32 : CP_V16) | CP_HE32 | CP_HI32, s));
   h->geo.tchunk = walk_chunk(h, p);
+  const int block = schur_block(h, p);
   switch (p) {
     case QXD_F64:
       launch_schur<double>(h, dagger, (double2*)out_e, (const double2*)in_e, h->t64, (const double2*)h->V64,
-                           (const double2*)h->He64, (const double2*)h->Hi64, norm_slot, schur_slices(h, p), schur_block(h, p), s);
+                           (const double2*)h->He64, (const double2*)h->Hi64, norm_slot, schur_slices(h, p), block, s);
       break;
     case QXD_F32:
       launch_schur<float>(h, dagger, (float4*)out_e, (const float4*)in_e, h->t32, (const float2*)h->V32,
-                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), schur_block(h, p), s);
+                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), block, s);
       break;
     case QXD_BF16:
       launch_schur<float>(h, dagger, (uint4*)out_e, (const uint4*)in_e, h->t16, (const uint32_t*)h->V16,
-                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), schur_block(h, p), s);
+                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), block, s);
       break;
     default:
       return QXD_EINVAL;

@@ -71,10 +71,12 @@ __device__ __forceinline__ void colour_mul(const cx<T> u[9], const cx<T> h0[3], 
   }
 }
 
-// Add (1 - g_MU) W s (FWD) or (1 + g_MU) W^+ s (backward) to acc, W the link u;
-// neg flips the sign (antiperiodic time wrap).
+// The multiplied two-spinor of one hop, (1 - g_MU) W s (FWD) or (1 + g_MU) W^+ s
+// (backward) before it is rebuilt, W the link u; neg flips the sign
+// (antiperiodic time wrap).
 template <int MU, bool FWD, class T>
-__device__ __forceinline__ void hop_term(cx<T> acc[12], const cx<T> s[12], const cx<T> u[9], bool neg) {
+__device__ __forceinline__ void hop_two_spinor(const cx<T> s[12], const cx<T> u[9], bool neg, cx<T> w0[3],
+                                               cx<T> w1[3]) {
   cx<T> h0[3], h1[3];
   spin_project<MU, FWD>(s, h0, h1);
   if (MU == 0 && neg) {
@@ -84,8 +86,14 @@ __device__ __forceinline__ void hop_term(cx<T> acc[12], const cx<T> s[12], const
       h1[a] = -h1[a];
     }
   }
-  cx<T> w0[3], w1[3];
   colour_mul<FWD>(u, h0, h1, w0, w1);
+}
+
+// Add the hop to acc.
+template <int MU, bool FWD, class T>
+__device__ __forceinline__ void hop_term(cx<T> acc[12], const cx<T> s[12], const cx<T> u[9], bool neg) {
+  cx<T> w0[3], w1[3];
+  hop_two_spinor<MU, FWD>(s, u, neg, w0, w1);
   spin_rebuild_add<MU, FWD>(acc, w0, w1);
 }
 
