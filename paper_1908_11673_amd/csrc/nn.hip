@@ -260,130 +260,190 @@ struct NnTapList {
   }
 };
 
-// The tap loop, fully unrolled: the weights of tap k + NN_WPF and the LDS
-// operands of tap k + APF are requested while tap k is contracted, on NCB
-// column tiles of 16 output channels starting at tile cb0; side(k) issues
-// further loads of the caller's (the next block's halo) in tap k.  raddr[rb][d3 + 1] is the byte
-// address of row rb's neighbour at (-1, -1, -1, d3); tap (d0, d1, d2, d3)
-// adds the constant (d0 + 1) T0 + (d1 + 1) T1 + (d2 + 1) T2.
-#ifndef NN_WPF
-#define NN_WPF 4  // taps ahead whose weights are in flight
-#endif
+// Weights of the tap loop.  Groups of taps pass through two LDS buffers of
+// eight tiles (a tap x 16 output channels, 64 lanes x 16 bytes in the order of
+// the matrix-core operand), which the eight waves fill a tile each: with all 81
+// taps, group g holds the taps 4 g .. 4 g + 3; with SPARSE, two taps of the list
+// of either parity.
+constexpr int kNnGroups = 21;
+constexpr int kNnWBuf = 8 * 1024;
+
+// first element of the weight tile that wave w brings for group g
+template <bool SPARSE>
+__device__ __forceinline__ int nn_stage_tile(int g, int w) {
+  int tap;
+  if constexpr (SPARSE) {
+    constexpr NnTapList<true, 0> L0{};
+    constexpr NnTapList<true, 1> L1{};
+    const int i0 = 2 * g < L0.n ? 2 * g : L0.n - 1, i1 = 2 * g + 1 < L0.n ? 2 * g + 1 : L0.n - 1;
+    const int j0 = 2 * g < L1.n ? 2 * g : L1.n - 1, j1 = 2 * g + 1 < L1.n ? 2 * g + 1 : L1.n - 1;
+    const int t0 = L0.t[i0], t1 = L0.t[i1], u0 = L1.t[j0], u1 = L1.t[j1];
+    tap = w & 4 ? (w & 2 ? u1 : u0) : (w & 2 ? t1 : t0);
+  } else {
+    tap = min(4 * g + (w >> 1), NN_TAPS - 1);
+  }
+  return tap * (NN_C * NN_C) + (w & 1) * 4 * NN_C;
+}
+
+// The tap loop, fully unrolled, on RB row tiles and both column tiles of 16
+// output channels: the LDS operands of the next tap (of two taps ahead with two
+// row tiles) are requested while a tap is contracted; side(k) issues further loads
+// of the caller's (the next block's halo) in tap k; stage(g) writes the weights of
+// group g + 1 to the LDS and requests those of group g + 3.  raddr[rb][d3 + 1]
+// is the byte address of row rb's neighbour at (-1, -1, -1, d3); tap (d0, d1,
+// d2, d3) adds the constant (d0 + 1) T0 + (d1 + 1) T1 + (d2 + 1) T2.
+// A group's barrier stands after the tap that requests its last weights: by
+// then every wave has read them (their buffer may be overwritten) and written
+// its tile of the next group.
 #ifndef NN_WAVES
 #define NN_WAVES 8  // waves per workgroup of the block kernel
 #endif
-#ifndef NN_APF
-#define NN_APF 2  // taps ahead whose LDS operands are in flight
-#endif
-template <class SH, bool SPARSE, int P, int RB, int NCB, class PF>
-__device__ __forceinline__ void nn_blk_taps(const char* lds, const uint16_t* __restrict__ W, const int (&raddr)[RB][3],
-                                            int lr, int kc, int cb0, f4v (&acc)[RB][NCB], PF&& side) {
+template <class SH, bool SPARSE, int P, int RB, class PF, class ST>
+__device__ __forceinline__ void nn_blk_taps(const char* lds, const char* wl, const int (&raddr)[RB][3],
+                                            f4v (&acc)[RB][2], PF&& side, ST&& stage) {
   constexpr NnTapList<SPARSE, P> TL{};
-  // LDS operands of APF taps ahead: 8 row tiles hold 32 registers per tap in flight
-  constexpr int APF = RB >= 8 ? 1 : NN_APF;
-  static_assert(TL.n > NN_WPF && TL.n > APF, "prefetch deeper than the tap list");
-  auto wld = [&](int tap, int cb) {
-    return ld8(W + tap * (NN_C * NN_C) + ((cb0 + cb) * 16 + lr) * NN_C + kc);
-  };
+  constexpr int GT = SPARSE ? 2 : 4, APF = RB >= 4 ? 1 : 2;
+  static_assert(APF < GT && (TL.n + GT - 1) / GT <= kNnGroups && TL.n > GT * (kNnGroups - 2), "groups of taps");
   auto rd = [&](int rb, int tap) {
     const int off = (tap / 27) * SH::T0 + (tap / 9 % 3) * SH::T1 + (tap / 3 % 3) * SH::T2;
     return *reinterpret_cast<const bf16x8*>(lds + raddr[rb][tap % 3] + off);
   };
-  bf16x8 wb[NN_WPF][NCB];
+  auto wrd = [&](int k, int cb) {
+    return *reinterpret_cast<const bf16x8*>(wl + (k / GT & 1) * kNnWBuf + (k % GT) * 2048 + cb * 1024);
+  };
+  bf16x8 a[APF + 1][RB], w[APF + 1][2];
 #pragma unroll
-  for (int k = 0; k < NN_WPF; ++k)
+  for (int k = 0; k < APF; ++k) {
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) wb[k][cb] = wld(TL.t[k], cb);
-  bf16x8 a[APF + 1][RB];
-#pragma unroll
-  for (int k = 0; k < APF; ++k)
+    for (int cb = 0; cb < 2; ++cb) w[k][cb] = wrd(k, cb);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) a[k][rb] = rd(rb, TL.t[k]);
+  }
   // an explicit count: a plain full-unroll request is dropped above LLVM's
   // size limit, which this loop body with its halo loads exceeds
-#pragma unroll TL.n
-  for (int k = 0; k < TL.n; ++k) {
-    bf16x8 w[NCB];
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) w[cb] = wb[k % NN_WPF][cb];
-    if (k + NN_WPF < TL.n) {
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) wb[k % NN_WPF][cb] = wld(TL.t[k + NN_WPF], cb);
-    }
+#pragma unroll GT * kNnGroups
+  for (int k = 0; k < GT * kNnGroups; ++k) {
+    if (k % GT == 0) stage(k / GT);
+    if (k >= TL.n) continue;
     side(k);
     if (k + APF < TL.n) {
 #pragma unroll
+      for (int cb = 0; cb < 2; ++cb) w[(k + APF) % (APF + 1)][cb] = wrd(k + APF, cb);
+#pragma unroll
       for (int rb = 0; rb < RB; ++rb) a[(k + APF) % (APF + 1)][rb] = rd(rb, TL.t[k + APF]);
     }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb)
-        acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[k % (APF + 1)][rb], w[cb], acc[rb][cb], 0, 0, 0);
+      for (int cb = 0; cb < 2; ++cb)
+        acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[k % (APF + 1)][cb], a[k % (APF + 1)][rb], acc[rb][cb],
+                                                              0, 0, 0);
     // keep each tap's prefetches in this tap: left free, the scheduler sinks
     // every load next to its first use to save registers, and each tap then
-    // waits for its own weights and LDS operands
+    // waits for its own operands
     __builtin_amdgcn_sched_barrier(0);
+    if (k % GT == GT - 1 - APF && k / GT < kNnGroups - 1) __syncthreads();
   }
 }
 
-// Halo of the block with origin o, moved through registers: this thread
-// moves chunk threadIdx & 3 of the positions threadIdx / 4 + GRP k, k < HPT.
-// Positions past the halo and skipped odd sites read the first site; they
-// are written to LDS but never read.
+// Halo of the block with origin o, moved through registers in HPT loads a
+// thread: CK of the sites inside the block's x3 extent (a wave takes two lines
+// along x3, neighbours in x2), and EK of the two sites beyond it on every line.
+// A table in LDS holds where each line and each site beyond its ends lies; 216
+// threads fill it once per block.  A load then takes some ten instructions; with its
+// address computed in place (75 vector ones a lane, or scalar ones a wave)
+// the tap loop of the middle layer took 34,900 cycles where it takes 26,000.
+// Loads past the halo repeat its last line or site; skipped odd sites read their
+// even neighbour, which lands where they would lie and is never read.
 template <class SH, int NW, bool SPARSE_IN>
 struct NnHalo {
-  static constexpr int GRP = 16 * NW;                     // positions per pass of the workgroup
-  static constexpr int HPT = (SH::NPOS + GRP - 1) / GRP;  // positions per thread
-  static_assert(HPT * GRP * 64 <= SH::LDS_BYTES, "halo staging");
-  __device__ static __forceinline__ uint4 load(const Geo& g, const uint16_t* __restrict__ in, int o0, int o1, int o2,
-                                               int o3, int k) {
-    int pos = (threadIdx.x >> 2) + GRP * k;
-    // opaque: otherwise the block-independent coordinates of all HPT
-    // positions are hoisted out of the block loop and held in registers
-    asm volatile("" : "+v"(pos));
-    bool ok = pos < SH::NPOS;
-    int h3 = pos % SH::H3, r = pos / SH::H3;
-    int h2 = r % SH::H2;
-    r /= SH::H2;
-    int h1 = r % SH::H1, h0 = r / SH::H1;
-    int x0 = o0 + h0 - 1, x1 = o1 + h1 - 1, x2 = o2 + h2 - 1, x3 = o3 + h3 - 1;
-    x0 = x0 < 0 ? x0 + g.Le0 : (x0 >= g.Le0 ? x0 - g.Le0 : x0);
-    x1 = x1 < 0 ? x1 + g.Le1 : (x1 >= g.Le1 ? x1 - g.Le1 : x1);
-    bool mir = false;
-    if (x2 < 0 || x2 >= g.Le2) {
-      x2 = x2 < 0 ? x2 + g.Le2 : x2 - g.Le2;
-      mir = g.cstar >= 2;
+  static_assert(SH::B3 == 8, "eight sites of a line for half a wave");
+  static constexpr int LINES = SH::H0 * SH::H1 * SH::H2, PAIRS = LINES / 2;
+  static constexpr int CK = (PAIRS + NW - 1) / NW;
+  static constexpr int EK = (2 * LINES + 16 * NW - 1) / (16 * NW);
+  static constexpr int HPT = CK + EK;
+  static constexpr int TABLE = 3 * LINES;  // words: the lines, then the ends of each
+  static_assert(LINES <= 64 * NW, "a thread per line");
+  // half index of the first site of each line inside the block, its parity in bit
+  // 31; site index of the site before and of the site behind
+  __device__ static __forceinline__ void table(const Geo& g, uint32_t* tbl, int o0, int o1, int o2, int o3) {
+    int line = threadIdx.x;
+    if (line >= LINES) return;
+    const int h2 = line % SH::H2, h1 = line / SH::H2 % SH::H1, h0 = line / (SH::H2 * SH::H1);
+    auto wrap = [](int x, int L) { return x < 0 ? x + L : (x >= L ? x - L : x); };
+    const int x0 = wrap(o0 + h0 - 1, g.Le0), x2 = o2 + h2 - 1, y2 = wrap(x2, g.Le2);
+    int x1 = wrap(o1 + h1 - 1, g.Le1);
+    if (x2 != y2 && g.cstar >= 2) x1 = geo_mirror_x1(g, x1);
+    tbl[line] = geo_half(g, x0, x1, y2, o3) | (uint32_t)((x0 + x1 + y2) & 1) << 31;
+#pragma unroll
+    for (int end = 0; end < 2; ++end) {
+      const int x3 = end ? o3 + SH::B3 : o3 - 1, y3 = wrap(x3, g.Le3);
+      const int y1 = x3 != y3 && g.cstar >= 3 ? geo_mirror_x1(g, x1) : x1;
+      const int par = (x0 + y1 + y2 + y3) & 1;
+      tbl[LINES + 2 * line + end] = geo_half(g, x0, y1, y2, y3) + (!SPARSE_IN && par ? g.Ve : 0);
     }
-    if (x3 < 0 || x3 >= g.Le3) {
-      x3 = x3 < 0 ? x3 + g.Le3 : x3 - g.Le3;
-      if (g.cstar >= 3) mir = !mir;
-    }
-    if (mir) x1 = geo_mirror_x1(g, x1);
-    int par = (x0 + x1 + x2 + x3) & 1;
-    ok = ok && !(SPARSE_IN && par);
-    size_t q = ok ? (size_t)par * g.Ve + geo_half(g, x0, x1, x2, x3) : 0;
-    return reinterpret_cast<const uint4*>(in + q * NN_C)[threadIdx.x & 3];
   }
-  __device__ static __forceinline__ void store(char* lds, int k, const uint4& v) {
-    int pos = (threadIdx.x >> 2) + GRP * k;
-    int h3 = pos % SH::H3;
-    *reinterpret_cast<uint4*>(lds + pos * 64 + (((threadIdx.x & 3) ^ ((h3 >> 1) & 3)) << 4)) = v;
+  // the table's word for load k
+  __device__ static __forceinline__ uint32_t entry(const uint32_t* tbl, int w, int k) {
+    const int l = threadIdx.x & 63;
+    if (k < CK) return tbl[2 * min(w + NW * k, PAIRS - 1) + (l >> 5)];
+    return tbl[LINES + min((int)(threadIdx.x >> 2) + 16 * NW * (k - CK), 2 * LINES - 1)];
+  }
+  __device__ static __forceinline__ uint4 load(const Geo& g, const uint16_t* __restrict__ in, uint32_t e, int k) {
+    const int l = threadIdx.x & 63;
+    uint32_t q = e;
+    if (k < CK) {
+      const int i3 = (l >> 2) & 7;  // x3 = o3 + i3
+      q = (e & 0x7fffffffu) + (i3 >> 1);
+      if (!SPARSE_IN) q += ((e >> 31) ^ i3) & 1 ? g.Ve : 0;
+    }
+    return reinterpret_cast<const uint4*>(in + (size_t)q * NN_C)[l & 3];
+  }
+  __device__ static __forceinline__ void store(char* lds, int w, int k, const uint4& v) {
+    const int l = threadIdx.x & 63;
+    int h0, h1, h2, h3;
+    if (k < CK) {
+      const int j = min(w + NW * k, PAIRS - 1);
+      h2 = 2 * (j % (SH::H2 / 2)) + (l >> 5);
+      h1 = j / (SH::H2 / 2) % SH::H1;
+      h0 = j / (SH::H2 / 2 * SH::H1);
+      h3 = 1 + ((l >> 2) & 7);
+    } else {
+      int e = (threadIdx.x >> 2) + 16 * NW * (k - CK);
+      // opaque: otherwise the addresses are hoisted out of the block loop and
+      // held in registers
+      asm volatile("" : "+v"(e));
+      e = min(e, 2 * LINES - 1);
+      h3 = e & 1 ? SH::H3 - 1 : 0;
+      e >>= 1;
+      h2 = e % SH::H2;
+      e /= SH::H2;
+      h1 = e % SH::H1;
+      h0 = e / SH::H1;
+    }
+    *reinterpret_cast<uint4*>(lds + nn_lds_addr<SH>(h0, h1, h2, h3, threadIdx.x & 3)) = v;
   }
 };
 
 // Persistent block-tiled convolution: a workgroup of NW = 8 waves (two per
 // SIMD, one workgroup per CU) walks blocks, and the workgroups of one XCD walk
 // one contiguous eighth of the block list together, so neighbouring blocks
-// share that XCD's L2.  A wave owns 8 row tiles of 16 same-parity sites (128
-// sites) and one column tile of 16 output channels, so each weight tile it
-// loads feeds 8 matrix-core instructions (the last layer: 4 tiles of even
-// sites).  Each operand read from LDS feeds one instruction: the LDS has the
-// bandwidth to spare, the vector memory path that brings the weights has
-// not (half the weight loads of a wave owning both column tiles of 4 row
-// tiles, for twice the LDS reads).  Per block: taps (with the next block's
-// halo loads), output tile staged in LDS, coalesced stores, the next halo
-// from registers to LDS.
+// share that XCD's L2.  A wave owns four row tiles of 16 same-parity sites (64
+// sites; the last layer two, of even sites) and both column tiles of 16 output
+// channels: six LDS operands, two of them weights, feed eight matrix-core
+// instructions.  The weights go through LDS too (nn_stage_tile): loaded by every
+// wave for itself they would wait, in the order of the vector memory counter, for the halo
+// loads issued before them.  The sites are the columns of the matrix-core result,
+// and a tile's output channels are chosen so that a lane ends with eight
+// consecutive ones, which it stores as they are.  Per block: taps (with the next
+// block's halo loads), output from the registers, the next halo from registers
+// to LDS.
+// Bound by the tap loop: the middle layer needs 20,736 matrix-core cycles a
+// block and SIMD and takes 28,000 of 32,000 in all.  At 64 x 32^3 (two parities, C*)
+// the layers take 379, 626 and 441 us (530, 749 and 569 with halo addresses
+// computed in the tap loop, weights loaded by each wave and the output through LDS);
+// at 32 x 16^3 31, 43 and 32 us (40, 52 and 41).
 template <int NW, int EPI, bool SPARSE_IN, bool EVEN_OUT>
 __global__ __launch_bounds__(64 * NW) void k_conv_ws(Geo g, int nblk, const uint16_t* __restrict__ in,
                                                  const uint16_t* __restrict__ W, uint16_t* __restrict__ out_act,
@@ -392,8 +452,12 @@ __global__ __launch_bounds__(64 * NW) void k_conv_ws(Geo g, int nblk, const uint
                                                  const float* __restrict__ rin, float skip,
                                                  const double* __restrict__ scal2, int i_s2) {
   using SH = NnBlock;
-  __shared__ uint4 lds4[SH::LDS_BYTES / 16];
-  char* lds = reinterpret_cast<char*>(lds4);
+  static_assert(NW == 8, "a weight tile of a group per wave");
+  using HL = NnHalo<SH, NW, SPARSE_IN>;
+  __shared__ uint4 lds4[(SH::LDS_BYTES + 2 * kNnWBuf) / 16];
+  __shared__ uint32_t tbl[HL::TABLE];
+  char* wlds = reinterpret_cast<char*>(lds4);  // the weights first, within reach of an LDS immediate
+  char* lds = wlds + 2 * kNnWBuf;
   const int n1 = g.Le1 / SH::B1, n2 = g.Le2 / SH::B2, n3 = g.Le3 / SH::B3;
   // this workgroup's blocks: group x = blockIdx % nx (the XCD when nx = 8) owns
   // blocks [x per, (x + 1) per), walked by its nwx workgroups in turn
@@ -413,15 +477,13 @@ __global__ __launch_bounds__(64 * NW) void k_conv_ws(Geo g, int nblk, const uint
     o3 = c3 * SH::B3;
   };
 
-  // NW waves share the 32 row tiles (16 of each parity) and the two column
-  // tiles, each wave one column tile; with EVEN_OUT the 16 even row tiles
-  constexpr int NCB = 1;
-  constexpr int RB = EVEN_OUT ? 32 / NW : 64 / NW;
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+  // NW waves share the 32 row tiles (16 of each parity; with EVEN_OUT the 16 even
+  // ones), each wave with both column tiles
+  constexpr int RB = (EVEN_OUT ? 16 : 32) / NW;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
   const int lr = l & 15, kc = (l >> 4) * 8, ch = l >> 4;
   const int p = EVEN_OUT ? 0 : wave / (NW / 2);
-  const int cb0 = wave & 1;
-  const int g0 = EVEN_OUT ? (wave >> 1) : (wave % (NW / 2)) >> 1, gstep = EVEN_OUT ? NW / 2 : NW / 4;
+  const int g0 = EVEN_OUT ? wave : wave % (NW / 2), gstep = EVEN_OUT ? NW : NW / 2;
   int raddr[RB][3];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -430,6 +492,16 @@ __global__ __launch_bounds__(64 * NW) void k_conv_ws(Geo g, int nblk, const uint
 #pragma unroll
     for (int d3 = 0; d3 < 3; ++d3) raddr[rb][d3] = nn_lds_addr<SH>(b0, b1, b2, b3 + d3, ch);
   }
+  // site index of this lane's row of the first row tile within a block at the
+  // origin, and the distance to the next row tile's
+  int hofs;
+  {
+    int b0, b1, b2, b3;
+    nn_blk_site<SH>(p, g0 * 16 + lr, b0, b1, b2, b3);
+    hofs = p * g.Ve + geo_half(g, b0, b1, b2, b3);
+  }
+  static_assert(NW / 2 * 16 % (SH::B1 * SH::B2 * SH::B3 / 2) == 0, "row tiles of a wave lie apart in x0 only");
+  const size_t hstep = (size_t)(gstep * 16 / (SH::B1 * SH::B2 * SH::B3 / 2)) * g.L3h * g.Le2 * g.Le1;
   float scale = 1.0f, skc = 0.0f;
   if (EPI == EPI_SPINOR) {
     if (scal) scale = (float)sqrt(scal[i_s]);
@@ -441,20 +513,48 @@ __global__ __launch_bounds__(64 * NW) void k_conv_ws(Geo g, int nblk, const uint
   // once its output tile has left: the loads of all workgroups then spread
   // over the matrix-core work instead of arriving at memory in one burst per
   // block.
-  using HL = NnHalo<SH, NW, SPARSE_IN>;
   // one halo load every HS taps, spread over the tap loop
   constexpr int NTAP0 = NnTapList<SPARSE_IN, 0>{}.n, NTAP1 = NnTapList<SPARSE_IN, 1>{}.n;
-  constexpr int HS = (NTAP0 < NTAP1 ? NTAP0 : NTAP1) / HL::HPT;
+  constexpr int GT = SPARSE_IN ? 2 : 4;  // the table is there from the second group of taps on
+  constexpr int HS = ((NTAP0 < NTAP1 ? NTAP0 : NTAP1) - GT) / HL::HPT;
   static_assert(HS >= 1, "one halo load per tap at most");
   uint4 hv[HL::HPT];
   if (bbeg + wi < bend) {
     int o0, o1, o2, o3;
     origin(bbeg + wi, o0, o1, o2, o3);
+    HL::table(g, tbl, o0, o1, o2, o3);
+    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < HL::HPT; ++k) hv[k] = HL::load(g, in, o0, o1, o2, o3, k);
+    for (int k = 0; k < HL::HPT; ++k) hv[k] = HL::load(g, in, HL::entry(tbl, wave, k), k);
 #pragma unroll
-    for (int k = 0; k < HL::HPT; ++k) HL::store(lds, k, hv[k]);
+    for (int k = 0; k < HL::HPT; ++k) HL::store(lds, wave, k, hv[k]);
   }
+  // weights on their way: group g in wr0 or wr1 by its parity, group 0 already in the LDS.  After
+  // the last group the next block's follow as groups 22, 23, ... (21 is empty),
+  // so that a group's buffer and register are known to the compiler.
+  // Row i of column tile c is output channel 8 (i / 4) + 4 c + i % 4: a lane of the
+  // result then holds eight consecutive channels of its site.
+  const int wrow = (8 * (lr >> 2) + (lr & 3)) * NN_C + kc;
+  uint4 wr0, wr1;
+  char* wst = wlds + wave * 1024 + l * 16;
+  const char* wl = wlds + (SPARSE_IN ? p * 4096 : 0) + l * 16;
+  auto wget = [&](const uint16_t* w, int gr) {
+    const uint4 v = *reinterpret_cast<const uint4*>(w + nn_stage_tile<SPARSE_IN>(gr % (kNnGroups + 1), wave) + wrow);
+    if (gr & 1)
+      wr1 = v;
+    else
+      wr0 = v;
+  };
+  auto wput = [&](int gr) {
+    if (gr & 1)
+      *reinterpret_cast<uint4*>(wst + kNnWBuf) = wr1;
+    else
+      *reinterpret_cast<uint4*>(wst) = wr0;
+  };
+  wget(W, 0);
+  wput(0);
+  wget(W, 1);
+  wget(W, 2);
   __syncthreads();
 
   for (int b = bbeg + wi; b < bend; b += nwx) {
@@ -463,14 +563,20 @@ __global__ __launch_bounds__(64 * NW) void k_conv_ws(Geo g, int nblk, const uint
     // the next block of this workgroup (the last one loads a block it does not use)
     int n0, n1h, n2h, n3h;
     origin(min(b + nwx, bend - 1), n0, n1h, n2h, n3h);
+    uint32_t he = 0;
     auto side = [&](int k) {
-      if (k % HS == 0 && k / HS < HL::HPT) hv[k / HS] = HL::load(g, in, n0, n1h, n2h, n3h, k / HS);
+      if (k == 0) HL::table(g, tbl, n0, n1h, n2h, n3h);
+      if (k < GT) return;
+      const int i = (k - GT) / HS;
+      if (i >= HL::HPT) return;
+      if ((k - GT) % HS == 0) he = HL::entry(tbl, wave, i);
+      if ((k - GT) % HS == HS - 1) hv[i] = HL::load(g, in, he, i);
     };
-    f4v acc[RB][NCB];
+    f4v acc[RB][2];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) acc[rb][cb] = f4v{0.f, 0.f, 0.f, 0.f};
+      for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = f4v{0.f, 0.f, 0.f, 0.f};
     // the weight loads do not depend on the block: keep the compiler from
     // hoisting all 81 taps' worth out of the block loop.  The opaque value is
     // an offset, not the pointer: a pointer passed through the asm loses its
@@ -480,87 +586,71 @@ __global__ __launch_bounds__(64 * NW) void k_conv_ws(Geo g, int nblk, const uint
     int wofs = 0;
     asm volatile("" : "+s"(wofs));
     const uint16_t* Wb = W + wofs;
+    auto stage = [&](int gr) {
+      if (gr + 1 < kNnGroups) wput(gr + 1);
+      if (gr + 3 != kNnGroups) wget(Wb, gr + 3);
+    };
     if (!SPARSE_IN || p == 0)
-      nn_blk_taps<SH, SPARSE_IN, 0, RB, NCB>(lds, Wb, raddr, lr, kc, cb0, acc, side);
+      nn_blk_taps<SH, SPARSE_IN, 0, RB>(lds, wl, raddr, acc, side, stage);
     else
-      nn_blk_taps<SH, SPARSE_IN, 1, RB, NCB>(lds, Wb, raddr, lr, kc, cb0, acc, side);
-    __syncthreads();  // every wave is done with the halo: the LDS takes the output tile
-    const int hb = geo_half(g, o0, o1, o2, o3);
-    if (EPI == EPI_SPINOR) {
-      // even sites only: tile [256][24] FP32, then float4 stores per (component group, site)
-      float* st = reinterpret_cast<float*>(lds);
+      nn_blk_taps<SH, SPARSE_IN, 1, RB>(lds, wl, raddr, acc, side, stage);
+    // this lane's sites and channels 8 ch .. 8 ch + 7 (see wget)
+    const size_t q0 = (size_t)(hofs + geo_half(g, o0, o1, o2, o3));
+    float4 r4[RB][2];
+    uint4 m[RB];
+    if (EPI == EPI_SPINOR && rin) {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            int j = (g0 + rb * gstep) * 16 + (l >> 4) * 4 + i;
-            int c = (cb0 + cb) * 16 + lr;
-            if (c < 24) st[j * 24 + c] = acc[rb][cb][i];
-          }
-      __syncthreads();
-#pragma unroll
-      for (int it = 0; it < 6 * 4 / NW; ++it) {
-        int idx = threadIdx.x + 64 * NW * it;
-        int j = idx % (NN_BLK_SITES / 2), slot = idx / (NN_BLK_SITES / 2);
-        int b0, b1, b2, b3;
-        nn_blk_site<SH>(0, j, b0, b1, b2, b3);
-        size_t o = (size_t)slot * g.Ve + hb + geo_half(g, b0, b1, b2, b3);
-        float4 v = *reinterpret_cast<const float4*>(st + j * 24 + slot * 4);
-        v.x *= scale;
-        v.y *= scale;
-        v.z *= scale;
-        v.w *= scale;
-        if (rin) {
-          float4 r4 = reinterpret_cast<const float4*>(rin)[o];
-          v.x += skc * r4.x;
-          v.y += skc * r4.y;
-          v.z += skc * r4.z;
-          v.w += skc * r4.w;
-        }
-        reinterpret_cast<float4*>(out_f)[o] = v;
-      }
-    } else {
-      // tile [512][32] bf16 (site s = parity * 256 + j), then 16-byte stores
-      uint16_t* st = reinterpret_cast<uint16_t*>(lds);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            int s = p * (NN_BLK_SITES / 2) + (g0 + rb * gstep) * 16 + (l >> 4) * 4 + i;
-            float vv = acc[rb][cb][i];
-            st[s * NN_C + (cb0 + cb) * 16 + lr] = f2bf(EPI == EPI_RELU ? fmaxf(vv, 0.f) : vv);
-          }
-      __syncthreads();
-#pragma unroll
-      for (int it = 0; it < 8 * 4 / NW; ++it) {
-        int idx = threadIdx.x + 64 * NW * it;
-        int s = idx >> 2, c = idx & 3;
-        int ps = s / (NN_BLK_SITES / 2), j = s % (NN_BLK_SITES / 2);
-        int b0, b1, b2, b3;
-        nn_blk_site<SH>(ps, j, b0, b1, b2, b3);
-        size_t q = (size_t)ps * g.Ve + hb + geo_half(g, b0, b1, b2, b3);
-        uint4 v = *reinterpret_cast<const uint4*>(st + s * NN_C + c * 8);
-        if (EPI == EPI_MASK) {
-          uint4 m = *reinterpret_cast<const uint4*>(mask + q * NN_C + c * 8);
-          uint32_t* vw = reinterpret_cast<uint32_t*>(&v);
-          const uint32_t* mw = reinterpret_cast<const uint32_t*>(&m);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            uint32_t keep = (bf16lo(mw[k]) > 0.f ? 0x0000ffffu : 0u) | (bf16hi(mw[k]) > 0.f ? 0xffff0000u : 0u);
-            vw[k] &= keep;
-          }
-        }
-        *reinterpret_cast<uint4*>(out_act + q * NN_C + c * 8) = v;
-      }
+        for (int i = 0; i < 2; ++i)
+          r4[rb][i] = reinterpret_cast<const float4*>(rin)[(size_t)min(2 * ch + i, 5) * g.Ve + q0 + rb * hstep];
     }
-    __syncthreads();  // the output tile has left the LDS
-    if (b + nwx < bend) {
+    if (EPI == EPI_MASK) {
 #pragma unroll
-      for (int k = 0; k < HL::HPT; ++k) HL::store(lds, k, hv[k]);
+      for (int rb = 0; rb < RB; ++rb) m[rb] = *reinterpret_cast<const uint4*>(mask + (q0 + rb * hstep) * NN_C + 8 * ch);
+    }
+    __syncthreads();  // every wave is done with the halo and the weights
+    wput(kNnGroups + 1);
+    wget(Wb, kNnGroups + 3);
+    // unconditional (the last block writes a halo that is not read): in a branch
+    // of their own the stores draw the loads out of the tap loop after them
+#pragma unroll
+    for (int k = 0; k < HL::HPT; ++k) HL::store(lds, wave, k, hv[k]);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const size_t q = q0 + rb * hstep;
+      if (EPI == EPI_SPINOR) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const f4v t = acc[rb][i];
+          float4 v = make_float4(t[0] * scale, t[1] * scale, t[2] * scale, t[3] * scale);
+          if (rin) {
+            v.x += skc * r4[rb][i].x;
+            v.y += skc * r4[rb][i].y;
+            v.z += skc * r4[rb][i].z;
+            v.w += skc * r4[rb][i].w;
+          }
+          if (ch < 3) reinterpret_cast<float4*>(out_f)[(size_t)(2 * ch + i) * g.Ve + q] = v;
+        }
+      } else {
+        uint32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          float lo = acc[rb][k >> 1][2 * (k & 1)], hi = acc[rb][k >> 1][2 * (k & 1) + 1];
+          if (EPI == EPI_RELU) {
+            lo = fmaxf(lo, 0.f);
+            hi = fmaxf(hi, 0.f);
+          }
+          v[k] = pack_bf16x2(lo, hi);
+        }
+        if (EPI == EPI_MASK) {
+          const uint32_t mw[4] = {m[rb].x, m[rb].y, m[rb].z, m[rb].w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            v[k] &= (bf16lo(mw[k]) > 0.f ? 0x0000ffffu : 0u) | (bf16hi(mw[k]) > 0.f ? 0xffff0000u : 0u);
+        }
+        *reinterpret_cast<uint4*>(out_act + q * NN_C + 8 * ch) = make_uint4(v[0], v[1], v[2], v[3]);
+      }
     }
     __syncthreads();
   }

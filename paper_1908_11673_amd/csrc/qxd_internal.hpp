@@ -158,7 +158,14 @@ __host__ __device__ inline uint32_t f32_to_bf16_bits(float f) {
 }
 __host__ __device__ inline float bf16_bits_to_f32(uint32_t b) { return __builtin_bit_cast(float, b << 16); }
 __host__ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
+#ifdef __HIP_DEVICE_COMPILE__
+  // one instruction (v_cvt_pk_bf16_f32, the same rounding) for some 19
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{lo, hi}, b2));
+#else
   return f32_to_bf16_bits(lo) | (f32_to_bf16_bits(hi) << 16);
+#endif
 }
 __host__ __device__ inline float bf16lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
 __host__ __device__ inline float bf16hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
