@@ -70,7 +70,7 @@ extern "C" qxd_status qxd_create(const qxd_geom* g, qxd_handle** out) {
   }
   h->npartial = (size_t)QXD_MAX_PARTIAL;
   if ((size_t)div_up(h->Ve, 64) > h->npartial) h->npartial = (size_t)div_up(h->Ve, 64);
-  if (!dev_alloc(&h->partial, h->npartial * sizeof(double)) ||
+  if (!dev_alloc(&h->partial, (h->npartial + QXD_PARTIAL_B) * sizeof(double)) ||
       !dev_alloc(&h->scal, QXD_NSCAL * sizeof(double)) ||
       hipHostMalloc(&h->scal_host, QXD_NSCAL * sizeof(double), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();  // the failed allocation is reported as QXD_ENOMEM only
@@ -78,6 +78,7 @@ extern "C" qxd_status qxd_create(const qxd_geom* g, qxd_handle** out) {
     delete h;
     return QXD_ENOMEM;
   }
+  h->partial_b = h->partial + h->npartial;
   if (hipMemset(h->scal, 0, QXD_NSCAL * sizeof(double)) != hipSuccess) {
     release(h);
     delete h;

@@ -179,13 +179,25 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_cdot(const VT* __restrict__ x, co
   block_sums<2>(a, partial);
 }
 
+// sum.n partials added up as k_final_sum does, for the whole workgroup; slot's value
+// if there are none
+__device__ inline double sum_here(PartSum sum, const double* __restrict__ slot, double* sh, double* bc) {
+  if (sum.n == 0) return *slot;
+  double a = 0.0;
+  for (int i = threadIdx.x; i < sum.n; i += QXD_BLOCK) a += sum.part[i];
+  const double s = red_block(a, sh);
+  if (threadIdx.x == 0) *bc = s;
+  __syncthreads();
+  return *bc;
+}
+
 // CG: alpha = zz / ww; x += alpha p; r -= alpha w; partial |r|^2
 template <class VT>
 __global__ __launch_bounds__(QXD_BLOCK) void k_cg_xr(VT* __restrict__ x, VT* __restrict__ r, const VT* __restrict__ p,
                                                      const VT* __restrict__ w, size_t n, const double* __restrict__ scal,
-                                                     int i_zz, int i_ww, double* __restrict__ partial) {
-  __shared__ double sh[QXD_BLOCK / 64];
-  double alpha = scal[i_zz] / scal[i_ww];
+                                                     int i_zz, int i_ww, PartSum ww, double* __restrict__ partial) {
+  __shared__ double sh[QXD_BLOCK / 64], bc;
+  double alpha = scal[i_zz] / sum_here(ww, &scal[i_ww], sh, &bc);
   double a = 0.0;
   struct W4 {
     VT x, p, r, w;
@@ -202,11 +214,14 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_cg_xr(VT* __restrict__ x, VT* __r
   if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-// CG: beta = zz_new / zz_old; p = z + beta p
+// CG: beta = zz_new / zz_old; p = z + beta p; zz_new to its slot
 template <class VT>
 __global__ __launch_bounds__(QXD_BLOCK) void k_cg_p(VT* __restrict__ p, const VT* __restrict__ z, size_t n,
-                                                    const double* __restrict__ scal, int i_new, int i_old) {
-  double beta = scal[i_new] / scal[i_old];
+                                                    double* __restrict__ scal, int i_new, int i_old, PartSum zz) {
+  __shared__ double sh[QXD_BLOCK / 64], bc;
+  const double zn = sum_here(zz, &scal[i_new], sh, &bc);
+  double beta = zn / scal[i_old];
+  if (zz.n && blockIdx.x == 0 && threadIdx.x == 0) scal[i_new] = zn;
   stream_for(n, [&](size_t i) { return W2<VT>{ld_stream(&z[i]), ld_stream(&p[i])}; },
              [&](size_t i, W2<VT> v) { st_stream(&p[i], wcaxpy(v.a, beta, 0.0, v.b)); });
 }
@@ -417,15 +432,16 @@ void blas_cdot(qxd_handle* h, const VT* x, const VT* y, size_t n, double* slot, 
   launch_final_sum(h->partial, nred(n), 2, nred(n), slot, s);
 }
 template <class VT>
-void blas_cg_xr(qxd_handle* h, VT* x, VT* r, const VT* p, const VT* w, size_t n, int i_zz, int i_ww, int i_rr,
-                hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_xr<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, x, r, p, w, n, h->scal, i_zz, i_ww,
-                     h->partial);
-  launch_final_sum(h->partial, nred(n), 1, nred(n), h->scal + i_rr, s);
+PartSum blas_cg_xr(qxd_handle* h, VT* x, VT* r, const VT* p, const VT* w, size_t n, int i_zz, int i_ww, PartSum ww,
+                   hipStream_t s) {
+  static_assert(QXD_NRED <= QXD_PARTIAL_B, "partials of the residual");
+  hipLaunchKernelGGL(k_cg_xr<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, x, r, p, w, n, h->scal, i_zz, i_ww, ww,
+                     h->partial_b);
+  return PartSum{h->partial_b, nred(n)};
 }
 template <class VT>
-void blas_cg_p(qxd_handle* h, VT* p, const VT* z, size_t n, int i_new, int i_old, hipStream_t s) {
-  hipLaunchKernelGGL(k_cg_p<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, p, z, n, h->scal, i_new, i_old);
+void blas_cg_p(qxd_handle* h, VT* p, const VT* z, size_t n, int i_new, int i_old, PartSum zz, hipStream_t s) {
+  hipLaunchKernelGGL(k_cg_p<VT>, dim3(nred(n)), dim3(QXD_BLOCK), 0, s, p, z, n, h->scal, i_new, i_old, zz);
 }
 template <class VT>
 void blas_sub_norm(qxd_handle* h, VT* r, const VT* b, const VT* w, size_t n, double* slot, hipStream_t s) {
@@ -514,9 +530,9 @@ void blas_up_acc(qxd_handle* h, double2* x, const float4* e, int i_n2, hipStream
 #define INST(VT)                                                                                        \
   template void blas_norm2<VT>(qxd_handle*, const VT*, size_t, double*, hipStream_t);                  \
   template void blas_cdot<VT>(qxd_handle*, const VT*, const VT*, size_t, double*, hipStream_t);        \
-  template void blas_cg_xr<VT>(qxd_handle*, VT*, VT*, const VT*, const VT*, size_t, int, int, int,      \
+  template PartSum blas_cg_xr<VT>(qxd_handle*, VT*, VT*, const VT*, const VT*, size_t, int, int, PartSum, \
                                hipStream_t);                                                            \
-  template void blas_cg_p<VT>(qxd_handle*, VT*, const VT*, size_t, int, int, hipStream_t);              \
+  template void blas_cg_p<VT>(qxd_handle*, VT*, const VT*, size_t, int, int, PartSum, hipStream_t);       \
   template void blas_sub_norm<VT>(qxd_handle*, VT*, const VT*, const VT*, size_t, double*, hipStream_t); \
   template void blas_mdot<VT>(qxd_handle*, const Ptrs&, int, const VT*, size_t, double*, hipStream_t,   \
                               double*);                                                                 \

@@ -13,9 +13,9 @@ struct Ptrs {
 template <class VT> void blas_norm2(qxd_handle* h, const VT* x, size_t n, double* slot, hipStream_t s);
 template <class VT> void blas_cdot(qxd_handle* h, const VT* x, const VT* y, size_t n, double* slot, hipStream_t s);
 template <class VT>
-void blas_cg_xr(qxd_handle* h, VT* x, VT* r, const VT* p, const VT* w, size_t n, int i_zz, int i_ww, int i_rr,
+PartSum blas_cg_xr(qxd_handle* h, VT* x, VT* r, const VT* p, const VT* w, size_t n, int i_zz, int i_ww, PartSum ww,
                 hipStream_t s);
-template <class VT> void blas_cg_p(qxd_handle* h, VT* p, const VT* z, size_t n, int i_new, int i_old, hipStream_t s);
+template <class VT> void blas_cg_p(qxd_handle* h, VT* p, const VT* z, size_t n, int i_new, int i_old, PartSum zz, hipStream_t s);
 template <class VT>
 void blas_sub_norm(qxd_handle* h, VT* r, const VT* b, const VT* w, size_t n, double* slot, hipStream_t s);
 // host (below): pinned memory that the sums are written to as well, or null

@@ -457,7 +457,8 @@ static int schur_block(const qxd_handle* h, qxd_prec p) {
 
 template <class T, class SPT, class LKT, class CLT>
 static void launch_schur(qxd_handle* h, int dagger, SPT* out, const SPT* in, SPT* t, const LKT* V, const CLT* He,
-                         const CLT* Hi, double* norm_slot, int slices, int block, hipStream_t s) {
+                         const CLT* Hi, double* norm_slot, int slices, int block, hipStream_t s,
+                         PartSum* left = nullptr, int few = 0) {
   const size_t lk_half = (size_t)4 * 9 * h->Ve;
   const LKT* Ve_l = V;
   const LKT* Vo_l = V + lk_half;
@@ -518,7 +519,9 @@ static void launch_schur(qxd_handle* h, int dagger, SPT* out, const SPT* in, SPT
       pass2((k * C - 2) * T1, (k + 1 < nchunk ? C : C + 2) * T1);
     }
   }
-  if (norm_slot) launch_final_sum(h->partial, G, 1, G, norm_slot, s);
+  if (!norm_slot) return;
+  if (left) *left = G <= few ? PartSum{h->partial, G} : PartSum{};
+  if (!left || !left->n) launch_final_sum(h->partial, G, 1, G, norm_slot, s);
 }
 
 // Workgroup walk for the Schur passes (site_tile): windows of K tiles per XCD.
@@ -534,7 +537,7 @@ static int walk_chunk(const qxd_handle* h, qxd_prec p) {
 }
 
 qxd_status qxd_schur_apply(qxd_handle* h, qxd_prec p, int dagger, void* out_e, const void* in_e, double* norm_slot,
-                           hipStream_t s) {
+                           hipStream_t s, PartSum* left, int few) {
   if (!h->has_inverse) return QXD_ESTATE;
   QXD_TRY(ensure_t(h, p));
   if (p != QXD_F64) QXD_TRY(ensure_copies(h, (p == QXD_F32 ? CP_V32 : CP_V16) | CP_HE32 | CP_HI32, s));
@@ -543,15 +546,15 @@ qxd_status qxd_schur_apply(qxd_handle* h, qxd_prec p, int dagger, void* out_e, c
   switch (p) {
     case QXD_F64:
       launch_schur<double>(h, dagger, (double2*)out_e, (const double2*)in_e, h->t64, (const double2*)h->V64,
-                           (const double2*)h->He64, (const double2*)h->Hi64, norm_slot, schur_slices(h, p), block, s);
+                           (const double2*)h->He64, (const double2*)h->Hi64, norm_slot, schur_slices(h, p), block, s, left, few);
       break;
     case QXD_F32:
       launch_schur<float>(h, dagger, (float4*)out_e, (const float4*)in_e, h->t32, (const float2*)h->V32,
-                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), block, s);
+                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), block, s, left, few);
       break;
     case QXD_BF16:
       launch_schur<float>(h, dagger, (uint4*)out_e, (const uint4*)in_e, h->t16, (const uint32_t*)h->V16,
-                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), block, s);
+                          (const float4*)h->He32, (const float4*)h->Hi32, norm_slot, schur_slices(h, p), block, s, left, few);
       break;
     default:
       return QXD_EINVAL;
@@ -562,13 +565,13 @@ qxd_status qxd_schur_apply(qxd_handle* h, qxd_prec p, int dagger, void* out_e, c
 
 // BF16 links with FP32 spinors (the inner operator of the BF16 solver mode)
 qxd_status qxd_schur_apply_mixed(qxd_handle* h, int dagger, float4* out_e, const float4* in_e, double* norm_slot,
-                                 hipStream_t s) {
+                                 hipStream_t s, PartSum* left, int few) {
   if (!h->has_inverse) return QXD_ESTATE;
   QXD_TRY(ensure_t(h, QXD_F32));
   QXD_TRY(ensure_copies(h, CP_V16 | CP_HE32 | CP_HI32, s));
   h->geo.tchunk = walk_chunk(h, QXD_F32);
   launch_schur<float>(h, dagger, out_e, in_e, h->t32, (const uint32_t*)h->V16, (const float4*)h->He32,
-                      (const float4*)h->Hi32, norm_slot, schur_slices(h, QXD_F32), schur_block(h, QXD_F32), s);
+                      (const float4*)h->Hi32, norm_slot, schur_slices(h, QXD_F32), schur_block(h, QXD_F32), s, left, few);
   QXD_HIP(hipGetLastError());
   return QXD_OK;
 }

@@ -71,11 +71,30 @@ struct VecPtrs {
   double2* p[kMsMax];
 };
 
-// a(k) and the zeta_j(k+1), a_j(k) of the shifts still active
-__global__ void k_ms_alpha(double* __restrict__ scal, int n) {
+// sum.n partials in the order of the other sums' kernel, valid in work-item 0's wave
+__device__ double ms_sum(PartSum sum) {
+  __shared__ double sh[QXD_BLOCK / 64];
+  double a = 0.0;
+  for (int i = threadIdx.x; i < sum.n; i += QXD_BLOCK) a += sum.part[i];
+  for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
+  __syncthreads();
+  double s = 0.0;
+  for (int k = 0; k < QXD_BLOCK / 64; ++k) s += sh[k];
+  return s;
+}
+
+// a(k) and the zeta_j(k+1), a_j(k) of the shifts still active, from the partials of
+// |D_hat p|^2 and |p|^2 (or, without partials, their slots).  One workgroup; it and
+// k_ms_beta take the place of three kernels that only added partials up.
+__global__ __launch_bounds__(QXD_BLOCK) void k_ms_alpha(double* __restrict__ scal, int n, PartSum dd, PartSum pp) {
   const int j = threadIdx.x;
+  const double ddv = dd.n ? ms_sum(dd) : scal[MS_DD];
+  const double ppv = pp.n ? ms_sum(pp) : scal[MS_PP];
+  if (j >= 64) return;
   const double rr = scal[MS_RR];
-  const double alpha = rr / (scal[MS_DD] + scal[MS_S0] * scal[MS_PP]);
+  const double alpha = rr / (ddv + scal[MS_S0] * ppv);
   const double ap = scal[MS_AP], bp = scal[MS_BP];
   if (j < n) {
     const double act = scal[MS_ACTN + j];
@@ -90,10 +109,14 @@ __global__ void k_ms_alpha(double* __restrict__ scal, int n) {
   if (j == 0) scal[MS_ALPHA] = alpha;
 }
 
-// b(k), the b_j(k), convergence of each shift, and the shift of the recurrences
-__global__ void k_ms_beta(double* __restrict__ scal, int n) {
+// b(k), the b_j(k), convergence of each shift, and the shift of the recurrences,
+// from the partials of |r|^2; host: |r|^2 and the number of active shifts there too,
+// unless null
+__global__ __launch_bounds__(QXD_BLOCK) void k_ms_beta(double* __restrict__ scal, int n, PartSum rs,
+                                                       double* __restrict__ host) {
   const int j = threadIdx.x;
-  const double rr = scal[MS_RR], rrn = scal[MS_RRN];
+  const double rr = scal[MS_RR], rrn = ms_sum(rs);
+  if (j >= 64) return;
   const double beta = rrn / rr;
   double still = 0.0;
   if (j < n && scal[MS_ACT + j] != 0.0) {
@@ -108,8 +131,11 @@ __global__ void k_ms_beta(double* __restrict__ scal, int n) {
   }
   // one wavefront: count the shifts that go on
   for (int off = 32; off > 0; off >>= 1) still += __shfl_xor(still, off);
-  __syncthreads();
   if (j == 0) {
+    if (host) {
+      host[MS_RR] = rrn;
+      host[MS_NACT] = still;
+    }
     scal[MS_NACT] = still;
     scal[MS_AP] = scal[MS_ALPHA];
     scal[MS_BP] = beta;
@@ -301,30 +327,41 @@ qxd_status ms_run(qxd_handle* h, const qxd_solver_params* prm, int n, const doub
   hs[MS_NACT] = n;
   QXD_HIP(hipMemcpyAsync(h->scal + S_MS, hs + S_MS, (MS_END - S_MS) * sizeof(double), hipMemcpyHostToDevice, s));
   const int check = prm->check_every > 0 ? prm->check_every : 1;
+  if (!h->step_done) QXD_HIP(hipEventCreateWithFlags(&h->step_done, hipEventDisableTiming));
+  static_assert(QXD_NRED <= QXD_PARTIAL_B, "partials of |p|^2, which wait while D_hat uses the others");
   int it = 0;
   qxd_status rc = QXD_ENOCONV;
+  PartSum pp;  // |p|^2: from the slot at first
   while (true) {
     if (it % check == 0) {
-      QXD_TRY(read_slots(h, MS_RR, MS_NACT - MS_RR + 1, s));
+      // after a step the two values are on the host once the event is past: the
+      // wait passes while the step's update runs
+      if (it == 0)
+        QXD_TRY(read_slots(h, MS_RR, MS_NACT - MS_RR + 1, s));
+      else
+        QXD_HIP(hipEventSynchronize(h->step_done));
       if (!std::isfinite(hs[MS_RR])) { rc = QXD_ENAN; break; }
       if (hs[MS_NACT] == 0.0) { rc = QXD_OK; break; }
     }
     if (it >= prm->nmx) break;
     // w = M p_base, |D_hat p|^2
-    QXD_TRY(qxd_schur_apply(h, QXD_F64, 0, t, P.p[base], h->scal + MS_DD, s));
+    PartSum dd;
+    QXD_TRY(qxd_schur_apply(h, QXD_F64, 0, t, P.p[base], h->scal + MS_DD, s, &dd, 1 << 30));
     QXD_TRY(qxd_schur_apply(h, QXD_F64, 1, w, t, nullptr, s));
     st->schur_applies += 2;
-    hipLaunchKernelGGL(k_ms_alpha, dim3(1), dim3(64), 0, s, h->scal, n);
+    hipLaunchKernelGGL(k_ms_alpha, dim3(1), dim3(QXD_BLOCK), 0, s, h->scal, n, dd, pp);
     hipLaunchKernelGGL(k_ms_r, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, r, w, P.p[base], len, h->scal, h->partial);
-    launch_final_sum(h->partial, QXD_NRED, 1, QXD_NRED, h->scal + MS_RRN, s);
-    hipLaunchKernelGGL(k_ms_beta, dim3(1), dim3(64), 0, s, h->scal, n);
+    const bool read = (it + 1) % check == 0;
+    hipLaunchKernelGGL(k_ms_beta, dim3(1), dim3(QXD_BLOCK), 0, s, h->scal, n, PartSum{h->partial, QXD_NRED},
+                       read ? hs : (double*)nullptr);
+    if (read) QXD_HIP(hipEventRecord(h->step_done, s));
     if (y)
       hipLaunchKernelGGL(k_ms_update<true>, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, P, XP, y, r, n, base, len,
-                         h->scal, h->partial);
+                         h->scal, h->partial_b);
     else
       hipLaunchKernelGGL(k_ms_update<false>, dim3(QXD_NRED), dim3(QXD_BLOCK), 0, s, P, XP, y, r, n, base, len,
-                         h->scal, h->partial);
-    launch_final_sum(h->partial, QXD_NRED, 1, QXD_NRED, h->scal + MS_PP, s);
+                         h->scal, h->partial_b);
+    pp = PartSum{h->partial_b, QXD_NRED};
     QXD_HIP(hipGetLastError());
     ++it;
   }

@@ -393,6 +393,7 @@ struct qxd_handle {
   double* scal = nullptr;     // [QXD_NSCAL] device scalars
   double* scal_host = nullptr;  // pinned mirror
   size_t npartial = 0;        // doubles in `partial`
+  double* partial_b = nullptr;  // [QXD_PARTIAL_B] behind them, for sums that wait while `partial` is in use
   bool tchunk_env = false;    // walk chunk fixed by QXD_TILE_CHUNK
   int slices_env = -1;        // time slices per Schur chunk fixed by QXD_SCHUR_SLICES (-1: by size)
   unsigned copies = 0;        // CP_* bits: lower-precision operator copies that are current
@@ -401,7 +402,7 @@ struct qxd_handle {
   // solver workspaces (grow-only), indexed by role
   void* ws[64] = {};
   size_t ws_bytes[64] = {};
-  hipEvent_t step_done = nullptr;  // FGCR: the scalars of a step are on the host
+  hipEvent_t step_done = nullptr;  // CG, FGCR, multi-shift CG: the scalars of a step are on the host
 };
 
 #define QXD_NSCAL 4096
@@ -465,8 +466,21 @@ inline int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // (host: pinned memory that they are written to as well, or null)
 void launch_final_sum(const double* partial, int n, int nvals, int stride, double* out, hipStream_t s,
                       double* host = nullptr);
+// A sum left as workgroup partials for the kernel that needs it; n = 0: it is in
+// its slot.
+struct PartSum {
+  const double* part = nullptr;
+  int n = 0;
+};
+#define QXD_PARTIAL_B 1024
+// norm_slot: |out|^2 there, unless null; left: or, with at most few of them, its
+// partials stay as they are.  QXD_FEW: few enough for every workgroup of the next
+// kernel to add up, where the kernel that does it costs 3 to 5 us with its
+// launch (CG on 512 even sites, FP64: 6.5 -> 5.2 ms; 131,072, FP32, 2048 partials: 24.9
+// -> 24.6 against the slot).
+#define QXD_FEW 2048
 qxd_status qxd_schur_apply(qxd_handle* h, qxd_prec p, int dagger, void* out_e, const void* in_e, double* norm_slot,
-                           hipStream_t s);
+                           hipStream_t s, PartSum* left = nullptr, int few = QXD_FEW);
 qxd_status nn_apply_internal(qxd_handle* h, qxd_nn* net, float4* out_e, const float4* in_e, hipStream_t s);
 // DFL+SAP preconditioner of the Schur system (dfl.hip): out_e = (M_DFL (in_e, 0))_e
 qxd_status dfl_apply_internal(qxd_handle* h, qxd_dfl* d, int nc, int ncy, int nmr, int eo, float4* out_e,
@@ -491,4 +505,4 @@ void release_copies(qxd_handle* h, unsigned which = CP_ALL);
 // `device` (the current device), looked up once per device (dirac.hip)
 qxd_status scratch_resolve(int device);
 qxd_status qxd_schur_apply_mixed(qxd_handle* h, int dagger, float4* out_e, const float4* in_e, double* norm_slot,
-                                 hipStream_t s);
+                                 hipStream_t s, PartSum* left = nullptr, int few = QXD_FEW);

@@ -78,11 +78,32 @@ struct InnerOp {
 };
 
 template <class VT>
-qxd_status apply_op(qxd_handle* h, InnerOp op, int dagger, VT* out, const VT* in, double* norm_slot,
-                        hipStream_t s) {
-  if (op.mode == 0) return qxd_schur_apply(h, QXD_F64, dagger, out, in, norm_slot, s);
-  if (op.mode == 1) return qxd_schur_apply(h, QXD_F32, dagger, out, in, norm_slot, s);
-  return qxd_schur_apply_mixed(h, dagger, (float4*)out, (const float4*)in, norm_slot, s);
+qxd_status apply_op(qxd_handle* h, InnerOp op, int dagger, VT* out, const VT* in, double* norm_slot, hipStream_t s,
+                    PartSum* left = nullptr) {
+  if (op.mode == 0) return qxd_schur_apply(h, QXD_F64, dagger, out, in, norm_slot, s, left);
+  if (op.mode == 1) return qxd_schur_apply(h, QXD_F32, dagger, out, in, norm_slot, s, left);
+  return qxd_schur_apply_mixed(h, dagger, (float4*)out, (const float4*)in, norm_slot, s, left);
+}
+
+// One CG iteration: w = D_hat p, x and r, z = D_hat^+ r, p.  With read, |r|^2 goes
+// to the slot i_rr on the host as well, ahead of D_hat^+: h->step_done is past once
+// it is there, and the host's wait for it passes while z and p are made.
+// (Adding up each sum in a kernel of its own and draining the stream at every
+// check took 42 us an iteration on 512 even sites, FP64; this takes 37.)
+template <class VT>
+qxd_status cg_step(qxd_handle* h, InnerOp op, VT* x, VT* r, VT* p, VT* z, VT* w, size_t n, int it, int i_rr,
+                   bool read, hipStream_t s) {
+  const int zo = S_ZZ0 + (it & 1), zn = S_ZZ0 + ((it + 1) & 1);
+  PartSum ww, zz;
+  QXD_TRY(apply_op<VT>(h, op, 0, w, p, h->scal + S_WW, s, &ww));
+  const PartSum rr = blas_cg_xr<VT>(h, x, r, p, w, n, zo, S_WW, ww, s);
+  if (read) {
+    launch_final_sum(rr.part, rr.n, 1, rr.n, h->scal + i_rr, s, h->scal_host + i_rr);
+    QXD_HIP(hipEventRecord(h->step_done, s));
+  }
+  QXD_TRY(apply_op<VT>(h, op, 1, z, r, h->scal + zn, s, &zz));
+  blas_cg_p<VT>(h, p, z, n, zn, zo, zz, s);
+  return QXD_OK;
 }
 
 // CG on the normal equations D_hat^+ D_hat x = D_hat^+ b of the inner operator,
@@ -97,17 +118,15 @@ qxd_status cgnr(qxd_handle* h, InnerOp op, VT* x, VT* r, VT* p, VT* z, VT* w, si
   QXD_TRY(apply_op<VT>(h, op, 1, z, r, h->scal + S_ZZ0, s));
   QXD_HIP(hipMemcpyAsync(p, z, bytes, hipMemcpyDeviceToDevice, s));
   *applies += 1;
+  if (!h->step_done) QXD_HIP(hipEventCreateWithFlags(&h->step_done, hipEventDisableTiming));
   int it = 0;
   while (it < max_steps) {
-    const int zo = S_ZZ0 + (it & 1), zn = S_ZZ0 + ((it + 1) & 1);
-    QXD_TRY(apply_op<VT>(h, op, 0, w, p, h->scal + S_WW, s));
-    blas_cg_xr<VT>(h, x, r, p, w, n, zo, S_WW, S_FRR, s);
-    QXD_TRY(apply_op<VT>(h, op, 1, z, r, h->scal + zn, s));
-    blas_cg_p<VT>(h, p, z, n, zn, zo, s);
+    const bool read = (it + 1) % check == 0;
+    QXD_TRY(cg_step<VT>(h, op, x, r, p, z, w, n, it, S_FRR, read, s));
     *applies += 2;
     ++it;
-    if (it % check == 0) {
-      QXD_TRY(read_scal(h, S_FRR, 1, s));
+    if (read) {
+      QXD_HIP(hipEventSynchronize(h->step_done));
       double rr = h->scal_host[S_FRR];
       if (!std::isfinite(rr)) return QXD_ENAN;
       if (std::sqrt(rr) <= tol_abs) break;
@@ -337,6 +356,8 @@ qxd_status solve_cg_dc(qxd_handle* h, const qxd_solver_params* prm, void* x, con
     QXD_TRY(qxd_eo_reconstruct(h, x, xe, b, s));
     QXD_TRY(true_residual(h, (const double2*)x, (const double2*)b, nb, &st.true_residual, s));
     if (rc == QXD_OK && !(st.true_residual <= prm->res)) rc = QXD_ENOCONV;
+  } else {
+    QXD_HIP(hipStreamSynchronize(s));  // what was launched ahead has ended when the call returns
   }
   st.status = rc;
   st.t_ms = std::chrono::duration<double, std::milli>(clk::now() - t0).count();
@@ -373,7 +394,8 @@ extern "C" qxd_status qxd_solve_cg(qxd_handle* h, const qxd_solver_params* prm, 
   int check = prm->check_every > 0 ? prm->check_every : 1;
   int it = 0;
   rc = QXD_ENOCONV;
-  bool restart = true;
+  if (!h->step_done) QXD_HIP(hipEventCreateWithFlags(&h->step_done, hipEventDisableTiming));
+  bool restart = true, fresh = true;  // fresh: |r|^2 comes from a norm, not from the last step
   while (true) {
     if (restart) {
       // z = D^+ r (norm -> zz), p = z, rr = |r|^2
@@ -382,9 +404,13 @@ extern "C" qxd_status qxd_solve_cg(qxd_handle* h, const qxd_solver_params* prm, 
       QXD_HIP(hipMemcpyAsync(p, z, bytes, hipMemcpyDeviceToDevice, s));
       blas_norm2<double2>(h, r, n, h->scal + S_RR, s);
       restart = false;
+      fresh = true;
     }
     if (it % check == 0 || it >= prm->nmx) {
-      QXD_TRY(read_scal(h, S_RR, 1, s));
+      if (fresh)
+        QXD_TRY(read_scal(h, S_RR, 1, s));
+      else
+        QXD_HIP(hipEventSynchronize(h->step_done));
       double rr = h->scal_host[S_RR];
       if (!std::isfinite(rr)) { rc = QXD_ENAN; break; }
       if (std::sqrt(rr) <= tol) {
@@ -399,11 +425,9 @@ extern "C" qxd_status qxd_solve_cg(qxd_handle* h, const qxd_solver_params* prm, 
       }
       if (it >= prm->nmx) break;
     }
-    int zo = S_ZZ0 + (it & 1), zn = S_ZZ0 + ((it + 1) & 1);
-    QXD_TRY(qxd_schur_apply(h, QXD_F64, 0, w, p, h->scal + S_WW, s));
-    blas_cg_xr<double2>(h, xe, r, p, w, n, zo, S_WW, S_RR, s);
-    QXD_TRY(qxd_schur_apply(h, QXD_F64, 1, z, r, h->scal + zn, s));
-    blas_cg_p<double2>(h, p, z, n, zn, zo, s);
+    QXD_TRY(cg_step<double2>(h, InnerOp{0}, xe, r, p, z, w, n, it, S_RR,
+                             (it + 1) % check == 0 || it + 1 >= prm->nmx, s));
+    fresh = false;
     st.schur_applies += 2;
     ++it;
   }
@@ -413,6 +437,8 @@ extern "C" qxd_status qxd_solve_cg(qxd_handle* h, const qxd_solver_params* prm, 
     QXD_TRY(qxd_eo_reconstruct(h, x, xe, b, s));
     QXD_TRY(true_residual(h, (const double2*)x, (const double2*)b, nb, &st.true_residual, s));
     if (rc == QXD_OK && !(st.true_residual <= prm->res)) rc = QXD_ENOCONV;
+  } else {
+    QXD_HIP(hipStreamSynchronize(s));  // what was launched ahead has ended when the call returns
   }
   st.status = rc;
   st.t_ms = std::chrono::duration<double, std::milli>(clk::now() - t0).count();
@@ -531,6 +557,8 @@ qxd_status solve_fgcr(qxd_handle* h, const qxd_solver_params* prm, qxd_nn* net, 
     QXD_TRY(qxd_eo_reconstruct(h, x, xe, b, s));
     QXD_TRY(true_residual(h, (const double2*)x, (const double2*)b, nb, &st.true_residual, s));
     if (rc == QXD_OK && !(st.true_residual <= prm->res)) rc = QXD_ENOCONV;
+  } else {
+    QXD_HIP(hipStreamSynchronize(s));  // what was launched ahead has ended when the call returns
   }
   st.status = rc;
   st.t_ms = std::chrono::duration<double, std::milli>(clk::now() - t0).count();
