@@ -23,6 +23,9 @@ extern "C" const char* qxd_status_string(qxd_status s) {
 }
 
 static void release(qxd_handle* h) {
+  // first: while the event holds its last kernels' launches, the runtime puts off
+  // freeing the memory they used, and the next handle's allocations pay for it
+  if (h->step_done) (void)hipEventDestroy(h->step_done);
   void* ptrs[] = {h->Uphys, h->Aphys, h->V64, h->V32, h->V16, h->He64, h->Ho64, h->Hi64, h->He32,
                   h->Ho32, h->Hi32, h->t64, h->t32, h->t16, h->partial, h->scal};
   for (void* p : ptrs)
@@ -30,7 +33,6 @@ static void release(qxd_handle* h) {
   for (int i = 0; i < 64; ++i)
     if (h->ws[i]) (void)hipFree(h->ws[i]);
   if (h->scal_host) (void)hipHostFree(h->scal_host);
-  if (h->step_done) (void)hipEventDestroy(h->step_done);
 }
 
 extern "C" qxd_status qxd_create(const qxd_geom* g, qxd_handle** out) {
