@@ -193,8 +193,8 @@ __global__ __launch_bounds__(256) void k_conv(Geo g, const uint16_t* __restrict_
 
 // ---------------------------------------------------------------------------
 // Block-tiled convolution.  The lattice is cut into B0 x B1 x B2 x B3 blocks
-// of 512 sites (every B even and dividing the extended extent, so the
-// block origin is an even site and local parity equals lattice parity).  The
+// of 512 sites (every B and every extent even, so the block origin is an even
+// site and local parity equals lattice parity; see NnBlocks).  The
 // block and its one-site halo are staged once in LDS, 64 bytes per site, so
 // with the 3^4 stencil each activation is fetched from memory about
 // (B+2)^4 / B^4 ~ 4 times instead of 81 times.  The halo follows the C*
@@ -227,6 +227,29 @@ struct NnShape {
 // t x x1 x x2 x x3 extents of the blocks: the x3 extent 8 keeps four
 // same-parity sites (256 contiguous bytes of activations) per x3 line
 typedef NnShape<4, 4, 4, 8> NnBlock;
+
+// The list of blocks that cover the extended lattice, x3 fastest.  Along a
+// direction whose extent the block's does not divide, the last block lies
+// back to the lattice's end, over its neighbour: the convolution writes the
+// sites of both the same values twice, the weight gradient leaves the first `skip`
+// of such a block out.
+struct NnBlocks {
+  int n[4];
+  __host__ __device__ explicit NnBlocks(const Geo& g)
+      : n{(g.Le0 + NnBlock::B0 - 1) / NnBlock::B0, (g.Le1 + NnBlock::B1 - 1) / NnBlock::B1,
+          (g.Le2 + NnBlock::B2 - 1) / NnBlock::B2, (g.Le3 + NnBlock::B3 - 1) / NnBlock::B3} {}
+  __host__ __device__ int64_t count() const { return (int64_t)n[0] * n[1] * n[2] * n[3]; }
+  __device__ void origin(const Geo& g, int b, int o[4], int skip[4]) const {
+    const int c3 = b % n[3], t = b / n[3], c2 = t % n[2], u = t / n[2];
+    const int c[4] = {u / n[1] * NnBlock::B0, u % n[1] * NnBlock::B1, c2 * NnBlock::B2, c3 * NnBlock::B3};
+    const int last[4] = {g.Le0 - NnBlock::B0, g.Le1 - NnBlock::B1, g.Le2 - NnBlock::B2, g.Le3 - NnBlock::B3};
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      o[m] = min(c[m], last[m]);
+      skip[m] = c[m] - o[m];
+    }
+  }
+};
 
 // byte address of chunk c of halo site h (see the layout above)
 template <class SH>
@@ -458,7 +481,7 @@ __global__ __launch_bounds__(64 * NW) void k_conv_ws(Geo g, int nblk, const uint
   __shared__ uint32_t tbl[HL::TABLE];
   char* wlds = reinterpret_cast<char*>(lds4);  // the weights first, within reach of an LDS immediate
   char* lds = wlds + 2 * kNnWBuf;
-  const int n1 = g.Le1 / SH::B1, n2 = g.Le2 / SH::B2, n3 = g.Le3 / SH::B3;
+  const NnBlocks blocks(g);
   // this workgroup's blocks: group x = blockIdx % nx (the XCD when nx = 8) owns
   // blocks [x per, (x + 1) per), walked by its nwx workgroups in turn
   const int nx = min(8, (int)gridDim.x);
@@ -467,14 +490,9 @@ __global__ __launch_bounds__(64 * NW) void k_conv_ws(Geo g, int nblk, const uint
   const int per = (nblk + nx - 1) / nx;
   const int bbeg = min(nblk, xcd * per), bend = min(nblk, (xcd + 1) * per);
   auto origin = [&](int b, int& o0, int& o1, int& o2, int& o3) {
-    int c3 = b % n3, t = b / n3;
-    int c2 = t % n2;
-    t /= n2;
-    int c1 = t % n1, c0 = t / n1;
-    o0 = c0 * SH::B0;
-    o1 = c1 * SH::B1;
-    o2 = c2 * SH::B2;
-    o3 = c3 * SH::B3;
+    int o[4], skip[4];
+    blocks.origin(g, b, o, skip);
+    o0 = o[0], o1 = o[1], o2 = o[2], o3 = o[3];
   };
 
   // NW waves share the 32 row tiles (16 of each parity; with EVEN_OUT the 16 even
@@ -889,8 +907,9 @@ struct WgRegs {
 constexpr int kWgIn = 144 * 4, kWgPieces = kWgIn + 64 * 4;
 
 __device__ __forceinline__ void wg_load(const Geo& g, const uint16_t* __restrict__ gq, const uint16_t* __restrict__ in,
-                                        int o0, int o1, int o2, int o3, int d0, WgRegs& R) {
+                                        const int (&o)[4], const int (&skip)[4], int d0, WgRegs& R) {
   const int cg = threadIdx.x & 3;
+  const int o0 = o[0], o1 = o[1], o2 = o[2], o3 = o[3];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int piece = threadIdx.x + 64 * kWgWaves * u;
@@ -926,6 +945,14 @@ __device__ __forceinline__ void wg_load(const Geo& g, const uint16_t* __restrict
         const size_t q = (size_t)((x0 + y1 + x2 + y3) & 1) * g.Ve + geo_half(g, x0, y1, x2, y3);
         R.e[k] = *reinterpret_cast<const u4v*>(f + q * NN_C);
       }
+    }
+    // what the block before has: rows of g, and the sites along x3 of `in`
+    if (skip[0] | skip[1] | skip[2] | skip[3]) {
+      const bool row_out = of_g && (row >> 4 < skip[0] || ((row >> 2) & 3) < skip[1] || (row & 3) < skip[2]);
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (of_g ? row_out : j < skip[3]) R.v[u][j] = u4v{0, 0, 0, 0};
+      if (row_out) R.e[0] = R.e[1] = u4v{0, 0, 0, 0};
     }
   }
 }
@@ -1015,14 +1042,15 @@ __global__ __launch_bounds__(64 * kWgWaves, 2) void k_wgrad_blk(Geo g, int nblk,
   __shared__ WgLds L;
   // neighbouring runs on one XCD
   const int unit = site_tile(blockIdx.x, gridDim.x, -1);
-  const int n1 = g.Le1 / SH::B1, n2 = g.Le2 / SH::B2, n3 = g.Le3 / SH::B3;
+  const NnBlocks blocks(g);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
   const int beg = unit * run, end = min(3 * nblk, beg + run);
   WgRegs R;
   auto load = [&](int item) {
     const int d0 = item / nblk - 1, b = item % nblk;
-    const int c3 = b % n3, c2 = b / n3 % n2, c1 = b / (n3 * n2) % n1, c0 = b / (n3 * n2 * n1);
-    wg_load(g, gq, in, c0 * SH::B0, c1 * SH::B1, c2 * SH::B2, c3 * SH::B3, d0, R);
+    int o[4], skip[4];
+    blocks.origin(g, b, o, skip);
+    wg_load(g, gq, in, o, skip, d0, R);
   };
   load(beg);
   for (int first = beg; first < end;) {
@@ -1096,7 +1124,7 @@ static qxd_status nn_repack(qxd_nn* net, hipStream_t s) {
 static void conv_launch_blk(qxd_handle* h, const qxd_nn* net, int layer, const uint16_t* in, const uint16_t* wl,
                             int epi, uint16_t* out_act, float* out_f, const uint16_t* mask, const double* scal, int i_s,
                             hipStream_t s, const float* rin, float skip, const double* scal2, int i_s2) {
-  const int nblk = (int)(h->V / NN_BLK_SITES);
+  const int nblk = (int)NnBlocks(h->geo).count();
   constexpr int NW = NN_WAVES;
   dim3 grid((unsigned)std::min(nblk, net->ncu)), blk(64 * NW);
   // the layer-1 input and the layer-3 output gradient vanish on odd sites
@@ -1144,10 +1172,15 @@ static void conv_launch(qxd_handle* h, int layer, const uint16_t* in, const uint
   }
 }
 
-// The tiled convolution runs when the 4 x 4 x 4 x 8 blocks divide the extended
-// lattice; otherwise the per-site gather kernel does.
+// The tiled convolution runs when a block of 4 x 4 x 4 x 8 fits into the
+// extended lattice; otherwise the per-site gather kernel does.  Blocks win however
+// much of them lies twice, as it can be most where there are few of them
+// (application, loss gradient of a pair against the gather kernels', us):
+// 6 x 6 x 6 x 10, a quarter of the blocks' sites used, 59, 229 against 140, 447;
+// 260 x 6 x 6 x 10, a third, 129, 493 against 181, 657; 34 x 36 x 20 x 34,
+// four fifths, 313, 1228 against 884, 3550.
 static bool nn_blocks_fit(const Geo& g) {
-  return g.Le0 % NnBlock::B0 == 0 && g.Le1 % NnBlock::B1 == 0 && g.Le2 % NnBlock::B2 == 0 && g.Le3 % NnBlock::B3 == 0;
+  return g.Le0 >= NnBlock::B0 && g.Le1 >= NnBlock::B1 && g.Le2 >= NnBlock::B2 && g.Le3 >= NnBlock::B3;
 }
 
 // free the buffers at ptrs and null them (a partly failed allocation leaves
@@ -1180,7 +1213,7 @@ static qxd_status nn_alloc_train(qxd_nn* net, hipStream_t s) {
   if (net->g3) return QXD_OK;
   qxd_handle* h = net->h;
   size_t bytes = (size_t)h->V * NN_C * sizeof(uint16_t);
-  const int nblk = (int)(h->V / NN_BLK_SITES);
+  const int nblk = (int)NnBlocks(h->geo).count();
   const int nchunk = net->blk ? div_up(nblk, wgrad_run(net, nblk)) + 1 : div_up(h->V, kWgChunk);
   if (!dev_alloc(&net->g3, bytes) || !dev_alloc(&net->gA, bytes) || !dev_alloc(&net->gB, bytes) ||
       !dev_alloc(&net->y, (size_t)h->Ve * 24 * sizeof(float)) ||
@@ -1225,7 +1258,7 @@ static void wgrad(qxd_handle* h, qxd_nn* net, const uint16_t* gq, const uint16_t
   const int cin = kCin[layer], cout = kCout[layer];
   int nchunk = 0, nblk = 0, run = 0;
   if (net->blk) {
-    nblk = (int)(h->V / NN_BLK_SITES);
+    nblk = (int)NnBlocks(h->geo).count();
     run = wgrad_run(net, nblk);
     hipLaunchKernelGGL(k_wgrad_blk, dim3(div_up(3 * (int64_t)nblk, run)), dim3(64 * kWgWaves), 0, s, h->geo, nblk, run, gq, in,
                        net->part);

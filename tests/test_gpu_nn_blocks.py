@@ -1,8 +1,9 @@
 """The block convolution against the per-site one where its walk over the blocks
 can go wrong: a single block (fewer workgroups than XCDs, every halo wrapping
 onto the block itself), a number of blocks that eight does not divide, C* shifts
-at block borders, and two blocks for each workgroup, whose halo table and
-weights are those of the next; forward, and the loss gradient, whose data
+at block borders, two blocks for each workgroup, whose halo table and
+weights are those of the next, and extents that the block's do not divide, along
+one direction and along all; forward, and the loss gradient, whose data
 gradients run the masked forms."""
 import os
 
@@ -16,7 +17,8 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 qxd = pytest.importorskip("paper_1908_11673_amd")
 
-GEOMS = [((4, 4, 4, 8), 0), ((12, 4, 8, 24), 0), ((8, 6, 8, 16), 2), ((20, 4, 12, 8), 3), ((32, 16, 16, 16), 3)]
+GEOMS = [((4, 4, 4, 8), 0), ((12, 4, 8, 24), 0), ((8, 6, 8, 16), 2), ((20, 4, 12, 8), 3), ((32, 16, 16, 16), 3),
+         ((4, 4, 4, 10), 0), ((6, 4, 4, 8), 1), ((4, 6, 6, 10), 1), ((6, 6, 6, 10), 3), ((10, 6, 14, 26), 2), ((22, 14, 18, 18), 3)]
 
 
 def network(lat, gather):
