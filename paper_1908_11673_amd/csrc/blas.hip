@@ -152,9 +152,7 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_final_sum(const double* __restric
                                                          double* __restrict__ out, double* __restrict__ host) {
   __shared__ double sh[QXD_BLOCK / 64];
   const int v = blockIdx.x;
-  double a = 0.0;
-  for (int i = threadIdx.x; i < n; i += QXD_BLOCK) a += partial[(size_t)v * stride + i];
-  double s = red_block(a, sh);
+  double s = red_block(partial_share(partial + (size_t)v * stride, n), sh);
   if (threadIdx.x == 0) {
     out[v] = s;
     if (host) host[v] = s;
@@ -183,9 +181,7 @@ __global__ __launch_bounds__(QXD_BLOCK) void k_cdot(const VT* __restrict__ x, co
 // if there are none
 __device__ inline double sum_here(PartSum sum, const double* __restrict__ slot, double* sh, double* bc) {
   if (sum.n == 0) return *slot;
-  double a = 0.0;
-  for (int i = threadIdx.x; i < sum.n; i += QXD_BLOCK) a += sum.part[i];
-  const double s = red_block(a, sh);
+  const double s = red_block(partial_share(sum.part, sum.n), sh);
   if (threadIdx.x == 0) *bc = s;
   __syncthreads();
   return *bc;

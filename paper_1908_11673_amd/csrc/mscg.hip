@@ -74,8 +74,7 @@ struct VecPtrs {
 // sum.n partials in the order of the other sums' kernel, valid in work-item 0's wave
 __device__ double ms_sum(PartSum sum) {
   __shared__ double sh[QXD_BLOCK / 64];
-  double a = 0.0;
-  for (int i = threadIdx.x; i < sum.n; i += QXD_BLOCK) a += sum.part[i];
+  double a = partial_share(sum.part, sum.n);
   for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;

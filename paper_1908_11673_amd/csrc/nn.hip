@@ -201,7 +201,7 @@ __global__ __launch_bounds__(256) void k_conv(Geo g, const uint16_t* __restrict_
 // neighbour map (a crossing of a k <= cstar boundary moves x1 by L1; two
 // crossings cancel).  Rows of one MFMA tile share a parity, so with an input
 // that vanishes on odd sites (SPARSE_IN) the taps landing on odd sites are
-// skipped for whole waves and odd halo sites are not loaded.  EVEN_OUT
+// skipped for whole waves and odd halo sites are not read.  EVEN_OUT
 // computes the even sites only (last layer).
 //
 // LDS layout: halo coordinates h = b + 1 in [0, B + 2); site (h0, h1, h2, h3)
@@ -845,7 +845,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(Geo g, const uint16_t* __res
 }
 
 // ---------------------------------------------------------------------------
-// Block-tiled weight gradient, where the 4 x 4 x 4 x 8 blocks divide the
+// Block-tiled weight gradient, where a 4 x 4 x 4 x 8 block fits into the
 // lattice.  With r = q + d3 e3, the gradient of tap d is
 //   sum_r g[r - d3 e3][co] in[r + (d0, d1, d2)][ci],
 // so with rows of 8 sites along x3 as the contraction index every operand of

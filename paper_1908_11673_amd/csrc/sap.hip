@@ -26,9 +26,9 @@
 // that each wavefront holds sites of one parity.  The
 // links (36 float2 a site, forward links of both parities), the clover blocks
 // (18 float4) and, on odd sites, their inverses are copied once per gauge field
-// and flavour; the iterate x and the source eta (6 float4) live in block order
-// for the whole application, and only the first and last half cycles touch the
-// half fields.
+// and flavour; the blocks' residuals and last solutions (6 float4 each) live in
+// block order for the whole application; a block's first half cycle reads the
+// source, and its solutions are summed in the half fields of the output.
 //
 // A workgroup of 256 threads owns one block, one thread per site; a site keeps
 // its four forward links in registers.  A hop exchange publishes the spinor of
