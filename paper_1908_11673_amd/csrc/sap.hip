@@ -26,9 +26,9 @@
 // that each wavefront holds sites of one parity.  The
 // links (36 float2 a site, forward links of both parities), the clover blocks
 // (18 float4) and, on odd sites, their inverses are copied once per gauge field
-// and flavour; the blocks' residuals and last solutions (6 float4 each) live in
-// block order for the whole application; a block's first half cycle reads the
-// source, and its solutions are summed in the half fields of the output.
+// and flavour; the iterate x and the source eta (6 float4) live in block order
+// for the whole application: the first half cycle reads the source, and each
+// block's last one writes x to the half fields of the output.
 //
 // A workgroup of 256 threads owns one block, one thread per site; a site keeps
 // its four forward links in registers.  A hop exchange publishes the spinor of
@@ -41,20 +41,27 @@
 // exchange suffices.  The block reductions of the minimal-residual step go
 // through LDS.
 //
-// The residual of a block is not formed again from x: it is what the last solve
-// left, plus the hops of the neighbours' last solutions across the faces, which
-// is all that changed since; so Eb holds the residuals, Xb the last solutions,
-// and x is summed in the caller's field.  The face hops run a wave a direction
-// on full waves.
+// The residual of a block is formed from x at every visit, through the same
+// exchange for the hops inside the block; the hops across its faces run a wave a
+// direction on full waves.  FP32 rounding of earlier solves is then part of what
+// the next one corrects.  Sums of hops start at zero and the clover product,
+// which is larger, is added to them last.  Relative error against complex128 at
+// 32 x 16^3, 2 cycles of 8 steps: 1.14e-7 plain, 1.16e-7 even-odd; with the
+// residual carried over from the last solve and the hops added to the clover
+// product 1.45e-7 and 1.67e-7, growing with the cycles.  (Carried, a plain
+// application at 64 x 32^3 took 3035 us where it takes 3110, an even-odd one of
+// 5 cycles at 32 x 16^3 655 where it takes 711.)
 //
-// What bounds it: vector instruction issue with plain blocks (counters: 93 % of
-// the cycles; 1420 instructions a site and step, of which the products,
-// projections and sums of the method are 1350).  64 x 32^3, 8 steps, first /
-// middle / last half cycle: 825 / 954 / 1068 -> 740 / 830 / 835 us.  The even-odd
-// blocks wait at three exchanges a step (45 % issue): 5 steps at 32 x 16^3, 512
-// blocks, 114 -> 68 us, of which 24 from the exchange without branches, 17 from
-// separate code for the waves of either parity (their registers no longer add
-// up) that works or loads while the other parity works.
+// What bounds it: vector instruction issue with plain blocks (95 % of the cycles
+// of the first half cycle, 87 % of those that form a residual; 1400 instructions
+// a site and step, of which the products, projections and sums of the method
+// are 1350).  64 x 32^3, 8 steps: the first half cycle 715 us, the first on the
+// other colour 767, later ones 880 to 895 (825, 954, 954 and 1068 with branches in
+// the exchange and face hops in the site's own work-item).  The even-odd blocks
+// wait at three exchanges a step (39 % issue): 5 steps at 32 x 16^3, 512 blocks, 72
+// us (114), 24 less by the exchange without branches and 17 by separate code for
+// the waves of either parity (their registers do not add up) that loads while
+// the other parity works.
 #include "blas.hpp"
 #include "sap_blocks.hpp"
 
@@ -227,13 +234,14 @@ __device__ __forceinline__ void sap_solve(SapLds& L, int t, int nmr, const float
                                           const cx<float> (*U)[9], cx<float> rho[12], cx<float> e[12]) {
   sap_zero(e);
   for (int step = 0; step < nmr; ++step) {
-    // v = -2 D_B rho = -2 H rho + hops(rho); every read of the previous step's
+    // v = -2 D_B rho = hops(rho) - 2 H rho; every read of the previous step's
     // exchange buffers came before its reduction barrier
     cx<float> v[12];
     sap_publish<false>(L, t, rho, U);
-    sap_clover<kSapSites>(cb, rho, v);
     __syncthreads();
+    sap_zero(v);
     sap_gather<false>(L, t, U, v);
+    sap_clover_add<kSapSites>(cb, rho, v);
     sap_step(sap_alpha<4>(L, t, v, rho), v, rho, e);
   }
 }
@@ -244,23 +252,28 @@ __device__ __forceinline__ void sap_solve(SapLds& L, int t, int nmr, const float
 // hold rho = r_e, then the Schur residual, and return e_e; the odd sites hold
 // rho = r_o and return e_o.  Sends and receives of one exchange touch the slots
 // of opposite parities, so a wave may publish right after it gathered.  While
-// the odd waves work the even ones multiply H_ee rho, while the even ones work
-// the odd ones request the clover inverse.
+// the even waves work the odd ones request the clover inverse.
 __device__ __forceinline__ void sap_solve_even(SapLds& L, int t, int nmr, bool odd_source,
                                                const float4* __restrict__ cb, const cx<float> (*U)[9],
                                                cx<float> rho[12], cx<float> e[12]) {
   __syncthreads();  // H_oo^-1 r_o / 2
   // r_e - D_eo H_oo^-1 r_o = r_e + hops(H_oo^-1 r_o / 2)
-  if (odd_source) sap_gather<true>(L, t, U, rho);
+  if (odd_source) {
+    sap_zero(e);  // free until the steps
+    sap_gather<true>(L, t, U, e);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) rho[c] = rho[c] + e[c];
+  }
   sap_zero(e);
   for (int step = 0; step < nmr; ++step) {
-    // v = -2 D_hat_B rho = -2 H_ee rho + hops(t_o), t_o = (1/2) H_oo^-1 hops(rho)
+    // v = -2 D_hat_B rho = hops(t_o) - 2 H_ee rho, t_o = (1/2) H_oo^-1 hops(rho)
     sap_publish<true>(L, t, rho, U);
     __syncthreads();
-    cx<float> v[12];
-    sap_clover<kSapSites>(cb, rho, v);
     __syncthreads();
+    cx<float> v[12];
+    sap_zero(v);
     sap_gather<true>(L, t, U, v);
+    sap_clover_add<kSapSites>(cb, rho, v);
     sap_step(sap_alpha<2>(L, t, v, rho), v, rho, e);
   }
   sap_publish<true>(L, t, e, U);
@@ -291,32 +304,27 @@ __device__ __forceinline__ void sap_solve_odd(SapLds& L, int t, int nmr, bool od
   }
   // e_o = H_oo^-1 (r_o - D_oe e_e) = (H_oo^-1 / 2) (2 r_o + hops(e_e))
   __syncthreads();
-#pragma unroll
-  for (int c = 0; c < 12; ++c) acc[c] = 2.f * rho[c];
+  sap_zero(acc);
   sap_gather<true>(L, t, U, acc);
+#pragma unroll
+  for (int c = 0; c < 12; ++c) acc[c] = 2.f * rho[c] + acc[c];
   sap_clover<S>(ci, acc, e);
 }
 
-// What a half cycle leaves besides the block solutions: SAP_OUT_NEW out = e,
-// SAP_OUT_SUM out = (the block's last e) + e, SAP_OUT_ADD out += e.
-enum { SAP_OUT_NONE = 0, SAP_OUT_NEW = 1, SAP_OUT_SUM = 2, SAP_OUT_ADD = 3 };
-
 // One half cycle on the blocks of `colour` (j = blockIdx.x; its partner is block
 // j of the other colour, the other block of the pair {2 k3, 2 k3 + 1} along x3).
-//   FIRST: the first of an application: the residual is the source, read from
-//          the even half field eta_e (and the odd half eta_o when given, else it
-//          is zero there), which is also written to Eb for the partner;
-//   else:  the block's residual is what it was left with when it was last solved
-//          (Eb; the source on the first visit of colour 1), plus the hops of the
-//          neighbours' last solutions (Xb) across the faces: all that changed.
-// Stored unless `last` (the block's last visit of the application): the
-// block's residual to Eb.  Xb gets the solution e unless nobody reads it
-// (keep_e).  EO: even-odd preconditioned block solves (waves 0, 1 hold the even
-// sites); they leave no residual on the odd sites, so Eb holds the even slots
-// only after the first visit.
+//   FIRST: the first of an application: x = 0, so the residual is the source,
+//          read from the even half field eta_e (and the odd half eta_o when
+//          given, else it is zero there) and copied to Eb for the block and its
+//          partner;
+//   else:  r = eta - D x from Eb and Xb; a block not yet visited has x = 0, and
+//          only the hops across its faces count.
+// last: the block's last visit: its x goes to out_e and, when given, out_o.  Xb
+// gets it unless nobody reads it (keep_x).  EO: even-odd preconditioned block
+// solves (waves 0, 1 hold the even sites).
 template <bool FIRST, bool EO>
-__global__ __launch_bounds__(kSapSites, 2) void k_sap_half(Geo g, SapGeo sb, int colour, int nmr, int out_mode,
-                                                           bool visited, bool last, bool keep_e,
+__global__ __launch_bounds__(kSapSites, 2) void k_sap_half(Geo g, SapGeo sb, int colour, int nmr,
+                                                           bool visited, bool last, bool keep_x,
                                                            const float4* __restrict__ eta_e,
                                                            float4* __restrict__ Eb, float4* __restrict__ Xb,
                                                            const float2* __restrict__ Vb,
@@ -332,7 +340,7 @@ __global__ __launch_bounds__(kSapSites, 2) void k_sap_half(Geo g, SapGeo sb, int
   const int B = colour * sb.nhalf + j;
   // EO: half the workgroups have their odd sites on waves 0, 1, so that the SIMDs
   // of a CU hold waves of both parities (with the even waves of both blocks on the
-  // same two SIMDs the others idle while they work: 71 -> 68 us)
+  // same two SIMDs the others idle while they work: 3 us more a half cycle)
   const int swap = EO && (((blockIdx.x >> 3) ^ (blockIdx.x >> 8)) & 1) ? kSapSites / 2 : 0;
   const SapSite w = sap_site<EO>(threadIdx.x ^ swap);
   // q: the site's parity (block origins are even), with EO the same in a wave
@@ -343,43 +351,6 @@ __global__ __launch_bounds__(kSapSites, 2) void k_sap_half(Geo g, SapGeo sb, int
   const float4* ci = CIb + (size_t)B * 18 * (kSapSites / 2) + (t - kSapSites / 2);  // odd slots only
   float4* xb = sap_blk<6>(Xb, B);
   float4* eb = sap_blk<6>(Eb, B);
-
-  cx<float> rho[12];
-  sap_zero(rho);
-  if (FIRST) {
-    if (q == 0 || eta_o) {
-      // the partner's site in the same slot (same parity: x3 moves by 4)
-      const int x3p = x3 + ((c[3] & 1) ? -kSapB : kSapB);
-      const float4* src = q ? eta_o : eta_e;
-      sp_load(src, Ve, geo_half(g, x0, x1, x2, x3), rho);
-      cx<float> ep[12];
-      sp_load(src, Ve, geo_half(g, x0, x1, x2, x3p), ep);
-      sp_store(sap_blk<6>(Eb, (1 - colour) * sb.nhalf + j), kSapSites, t, ep);
-    }
-  } else {
-    SapFace* face = reinterpret_cast<SapFace*>(L.bw);
-    static_assert(4 * sizeof(SapFace) <= sizeof(L.bw), "face hops");
-    if (t < 48) face[t / 12][t / 6 & 1][t % 6][kFaceZero] = make_float2(0.f, 0.f);
-    const int lane = t & 63;
-    switch (__builtin_amdgcn_readfirstlane(t >> 6)) {
-      case 0: sap_face_hops<0, EO>(g, sb, c, B, lane, Xb, Vb, face); break;
-      case 1: sap_face_hops<1, EO>(g, sb, c, B, lane, Xb, Vb, face); break;
-      case 2: sap_face_hops<2, EO>(g, sb, c, B, lane, Xb, Vb, face); break;
-      default: sap_face_hops<3, EO>(g, sb, c, B, lane, Xb, Vb, face); break;
-    }
-    if (q == 0 || (visited ? !EO : eta_o != nullptr)) sp_load(eb, kSapSites, t, rho);
-    __syncthreads();
-    cx<float> acc[12];
-    sap_zero(acc);
-    sap_face_add<0>(face, w, acc);
-    sap_face_add<1>(face, w, acc);
-    sap_face_add<2>(face, w, acc);
-    sap_face_add<3>(face, w, acc);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) rho[k] = rho[k] + 0.5f * acc[k];
-    __syncthreads();  // the exchange buffers take the place of the faces
-  }
-  sap_lds_init(L);
 
   // the site's four forward links stay in registers for the whole solve
   cx<float> U[4][9];
@@ -393,6 +364,58 @@ __global__ __launch_bounds__(kSapSites, 2) void k_sap_half(Geo g, SapGeo sb, int
         U[mu][k] = mk(v.x, v.y);
       }
   }
+  cx<float> rho[12];
+  sap_zero(rho);
+  if (FIRST) {
+    if (q == 0 || eta_o) {
+      // the partner's site in the same slot (same parity: x3 moves by 4)
+      const int x3p = x3 + ((c[3] & 1) ? -kSapB : kSapB);
+      const float4* src = q ? eta_o : eta_e;
+      sp_load(src, Ve, geo_half(g, x0, x1, x2, x3), rho);
+      if (!last) sp_store(eb, kSapSites, t, rho);
+      cx<float> ep[12];
+      sp_load(src, Ve, geo_half(g, x0, x1, x2, x3p), ep);
+      sp_store(sap_blk<6>(Eb, (1 - colour) * sb.nhalf + j), kSapSites, t, ep);
+    }
+    sap_lds_init(L);
+  } else {
+    cx<float> acc[12];
+    sap_zero(acc);
+    if (visited) {
+      cx<float> xs[12];
+      sp_load(xb, kSapSites, t, xs);
+      sap_lds_init(L);
+      sap_publish<EO>(L, t, xs, U);
+      __syncthreads();
+      sap_gather<EO>(L, t, U, acc);
+      __syncthreads();  // the faces take the place of the exchange buffers
+    }
+    SapFace* face = reinterpret_cast<SapFace*>(L.bw);
+    static_assert(4 * sizeof(SapFace) <= sizeof(L.bw), "face hops");
+    if (t < 48) face[t / 12][t / 6 & 1][t % 6][kFaceZero] = make_float2(0.f, 0.f);
+    const int lane = t & 63;
+    switch (__builtin_amdgcn_readfirstlane(t >> 6)) {
+      case 0: sap_face_hops<0, EO>(g, sb, c, B, lane, Xb, Vb, face); break;
+      case 1: sap_face_hops<1, EO>(g, sb, c, B, lane, Xb, Vb, face); break;
+      case 2: sap_face_hops<2, EO>(g, sb, c, B, lane, Xb, Vb, face); break;
+      default: sap_face_hops<3, EO>(g, sb, c, B, lane, Xb, Vb, face); break;
+    }
+    if (q == 0 || eta_o) sp_load(eb, kSapSites, t, rho);
+    __syncthreads();
+    sap_face_add<0>(face, w, acc);
+    sap_face_add<1>(face, w, acc);
+    sap_face_add<2>(face, w, acc);
+    sap_face_add<3>(face, w, acc);
+    if (visited) {
+      cx<float> xs[12];
+      sp_load(xb, kSapSites, t, xs);
+      sap_clover_add<kSapSites>(cb, xs, acc);
+    }
+#pragma unroll
+    for (int k = 0; k < 12; ++k) rho[k] = rho[k] + 0.5f * acc[k];
+    __syncthreads();  // the exchange buffers take the place of the faces
+    sap_lds_init(L);
+  }
 
   cx<float> e[12];  // the block solution
   if (!EO) {
@@ -402,24 +425,14 @@ __global__ __launch_bounds__(kSapSites, 2) void k_sap_half(Geo g, SapGeo sb, int
   } else {
     sap_solve_odd(L, t, nmr, !FIRST || eta_o, ci, U, rho, e);
   }
-  if (!last && (!EO || q == 0)) sp_store(eb, kSapSites, t, rho);
-  if (out_mode != SAP_OUT_NONE && (q == 0 || out_o)) {
-    float4* dst = q ? out_o : out_e;
-    const int h = geo_half(g, x0, x1, x2, x3);
+  if (visited) {
     cx<float> xs[12];
-    if (out_mode == SAP_OUT_SUM)
-      sp_load(xb, kSapSites, t, xs);
-    else if (out_mode == SAP_OUT_ADD)
-      sp_load(dst, Ve, h, xs);
-    if (out_mode == SAP_OUT_NEW)
-      sp_store(dst, Ve, h, e);
-    else {
+    sp_load(xb, kSapSites, t, xs);
 #pragma unroll
-      for (int k = 0; k < 12; ++k) xs[k] = xs[k] + e[k];
-      sp_store(dst, Ve, h, xs);
-    }
+    for (int k = 0; k < 12; ++k) e[k] = e[k] + xs[k];
   }
-  if (keep_e) sp_store(xb, kSapSites, t, e);
+  if (last && (q == 0 || out_o)) sp_store(q ? out_o : out_e, Ve, geo_half(g, x0, x1, x2, x3), e);
+  if (keep_x) sp_store(xb, kSapSites, t, e);
 }
 
 // workspace roles (free in the solvers' table): block-order links, clover
@@ -443,8 +456,7 @@ struct SapArgs {
 template <bool FIRST, bool EO>
 void sap_launch(const SapArgs& a, int cy, int ncy, int colour, hipStream_t s) {
   const bool last = cy == ncy - 1;
-  const int out = cy == 0 ? (last ? SAP_OUT_NEW : SAP_OUT_NONE) : cy == 1 ? SAP_OUT_SUM : SAP_OUT_ADD;
-  hipLaunchKernelGGL((k_sap_half<FIRST, EO>), dim3(a.sb.nhalf), dim3(kSapSites), 0, s, a.g, a.sb, colour, a.nmr, out,
+  hipLaunchKernelGGL((k_sap_half<FIRST, EO>), dim3(a.sb.nhalf), dim3(kSapSites), 0, s, a.g, a.sb, colour, a.nmr,
                      cy > 0, last, !(last && colour == 1), a.eta_e, a.Eb, a.Xb, a.Vb, a.Cb, a.CIb, a.out_e, a.eta_o,
                      a.out_o);
 }

@@ -128,11 +128,9 @@ __device__ __forceinline__ void sap_hop_term(cx<float> acc[12], const cx<float> 
   spin_rebuild_add<MU, FWD>(acc, w0, w1);
 }
 
-// out[0..5] = H in[0..5] for one packed Hermitian 6 x 6 block b (36 reals:
+// out += (H - diagonal) in for one packed Hermitian 6 x 6 block b (36 reals:
 // the diagonal, then the entries (i, j), i < j, row by row)
-__device__ __forceinline__ void sap_herm6(const float* b, const cx<float>* in, cx<float>* out) {
-#pragma unroll
-  for (int i = 0; i < 6; ++i) out[i] = b[i] * in[i];
+__device__ __forceinline__ void sap_herm6_off(const float* b, const cx<float>* in, cx<float>* out) {
   int k = 6;
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
@@ -144,6 +142,21 @@ __device__ __forceinline__ void sap_herm6(const float* b, const cx<float>* in, c
       sap_cmac_conj(out[j], hij, in[i]);
     }
   }
+}
+// out[0..5] = H in[0..5]
+__device__ __forceinline__ void sap_herm6(const float* b, const cx<float>* in, cx<float>* out) {
+#pragma unroll
+  for (int i = 0; i < 6; ++i) out[i] = b[i] * in[i];
+  sap_herm6_off(b, in, out);
+}
+// out[0..5] += H in[0..5]
+__device__ __forceinline__ void sap_herm6_add(const float* b, const cx<float>* in, cx<float>* out) {
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    out[i].re = fmaf(b[i], in[i].re, out[i].re);
+    out[i].im = fmaf(b[i], in[i].im, out[i].im);
+  }
+  sap_herm6_off(b, in, out);
 }
 
 // One 6 x 6 block of a site (36 registers), HALF its chirality.  Plain (cached)
@@ -169,6 +182,16 @@ __device__ __forceinline__ void sap_clover(const float4* __restrict__ cb, const 
   sap_herm6(r, in, out);
   sap_clover_load<STRIDE, 1>(cb, r);
   sap_herm6(r, in + 6, out + 6);
+}
+
+template <int STRIDE>
+__device__ __forceinline__ void sap_clover_add(const float4* __restrict__ cb, const cx<float> in[12],
+                                               cx<float> out[12]) {
+  float r[36];
+  sap_clover_load<STRIDE, 0>(cb, r);
+  sap_herm6_add(r, in, out);
+  sap_clover_load<STRIDE, 1>(cb, r);
+  sap_herm6_add(r, in + 6, out + 6);
 }
 
 // The backward hop that site t contributes to its forward neighbour along MU:
