@@ -1032,11 +1032,24 @@ __device__ __forceinline__ void wg_contract(const WgLds& L, int w, f16v (&acc)[4
 }
 
 // The work is the list of (d0, block) items, d0 slowest; workgroup u takes items
-// run u .. run u + run - 1 and leaves a partial sum for each d0 among them, in
-// slot u - wg_first(d0) of that d0.
-__host__ __device__ inline int wg_first(int nblk, int run, int i0) { return (int)((int64_t)i0 * nblk / run); }
+// run u .. run u + run - 1, and every len of them (counted from its first) it
+// leaves the partial sum of each d0 among them.  The sums are numbered by
+// wg_sum(item); that of d0 is in slot wg_sum(item) - wg_sum(its first item) of d0.
+// len: 2048 terms in one FP32 sum, as many as a chunk of k_conv_wgrad: four
+// blocks, or eight where the input or the gradient vanishes on half the sites
+// (layers 1 and 3).  The loss gradient of 4 pairs at 32 x 16^3 takes 2210 us, 2177
+// with eight everywhere and 2229 with four.
+constexpr int kWgLen = kWgChunk / NN_BLK_SITES;
+__host__ __device__ inline int wg_sum(int run, int len, int item) {
+  return item / run * ((run + len - 1) / len) + item % run / len;
+}
+// partial sums of d0 number i0
+__host__ __device__ inline int wg_sums(int nblk, int run, int len, int i0) {
+  return wg_sum(run, len, (i0 + 1) * nblk - 1) - wg_sum(run, len, i0 * nblk) + 1;
+}
 
-__global__ __launch_bounds__(64 * kWgWaves, 2) void k_wgrad_blk(Geo g, int nblk, int run, const uint16_t* __restrict__ gq,
+__global__ __launch_bounds__(64 * kWgWaves, 2) void k_wgrad_blk(Geo g, int nblk, int run, int len,
+                                                      const uint16_t* __restrict__ gq,
                                                       const uint16_t* __restrict__ in, float* __restrict__ part) {
   using SH = NnBlock;
   __shared__ WgLds L;
@@ -1054,7 +1067,8 @@ __global__ __launch_bounds__(64 * kWgWaves, 2) void k_wgrad_blk(Geo g, int nblk,
   };
   load(beg);
   for (int first = beg; first < end;) {
-    const int i0 = first / nblk, last = min(end, (i0 + 1) * nblk);
+    const int i0 = first / nblk;
+    const int last = min(min(end, (i0 + 1) * nblk), first + len - (first - beg) % len);
     f16v acc[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
@@ -1067,7 +1081,7 @@ __global__ __launch_bounds__(64 * kWgWaves, 2) void k_wgrad_blk(Geo g, int nblk,
       wg_contract(L, w, acc);
       __syncthreads();  // every wave is done with the rows
     }
-    float* o = part + ((size_t)(unit - wg_first(nblk, run, i0)) * NN_TAPS + 27 * i0) * (NN_C * NN_C);
+    float* o = part + ((size_t)(wg_sum(run, len, first) - wg_sum(run, len, i0 * nblk)) * NN_TAPS + 27 * i0) * (NN_C * NN_C);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       if (t == 3 && w >= 3) break;
@@ -1084,15 +1098,12 @@ __global__ __launch_bounds__(64 * kWgWaves, 2) void k_wgrad_blk(Geo g, int nblk,
 
 // grad[off + (tap cout + co) cin + ci] += sum over the partial sums of the tap
 // (fixed order): nchunk of them, or (run > 0) those of k_wgrad_blk
-__global__ void k_wgrad_reduce(const float* __restrict__ part, int nchunk, int nblk, int run, int cin, int cout,
-                               int off, float* __restrict__ grad) {
+__global__ void k_wgrad_reduce(const float* __restrict__ part, int nchunk, int nblk, int run, int len, int cin,
+                               int cout, int off, float* __restrict__ grad) {
   int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= NN_TAPS * cout * cin) return;
   int tap = t / (cout * cin), co = (t / cin) % cout, ci = t % cin;
-  if (run > 0) {
-    const int i0 = tap / 27;
-    nchunk = (int)(((int64_t)(i0 + 1) * nblk - 1) / run) - wg_first(nblk, run, i0) + 1;
-  }
+  if (run > 0) nchunk = wg_sums(nblk, run, len, tap / 27);
   const float* p = part + (size_t)tap * (NN_C * NN_C) + co * NN_C + ci;
   double s = 0.0;
 #pragma unroll 16
@@ -1205,7 +1216,7 @@ static qxd_status nn_alloc_act(qxd_nn* net, hipStream_t s) {
 }
 
 // Items of a workgroup of k_wgrad_blk: one round of the chip (a workgroup a
-// CU), and at most 8 blocks (4096 sites) in one FP32 sum.
+// CU), at most 8.
 static int wgrad_run(const qxd_nn* net, int nblk) { return std::min(8, div_up(3 * (int64_t)nblk, net->ncu)); }
 
 static qxd_status nn_alloc_train(qxd_nn* net, hipStream_t s) {
@@ -1214,7 +1225,11 @@ static qxd_status nn_alloc_train(qxd_nn* net, hipStream_t s) {
   qxd_handle* h = net->h;
   size_t bytes = (size_t)h->V * NN_C * sizeof(uint16_t);
   const int nblk = (int)NnBlocks(h->geo).count();
-  const int nchunk = net->blk ? div_up(nblk, wgrad_run(net, nblk)) + 1 : div_up(h->V, kWgChunk);
+  int nchunk = div_up(h->V, kWgChunk);
+  if (net->blk) {
+    nchunk = 0;
+    for (int i0 = 0; i0 < 3; ++i0) nchunk = std::max(nchunk, wg_sums(nblk, wgrad_run(net, nblk), kWgLen, i0));
+  }
   if (!dev_alloc(&net->g3, bytes) || !dev_alloc(&net->gA, bytes) || !dev_alloc(&net->gB, bytes) ||
       !dev_alloc(&net->y, (size_t)h->Ve * 24 * sizeof(float)) ||
       !dev_alloc(&net->dv, (size_t)h->Ve * 24 * sizeof(float)) ||
@@ -1257,19 +1272,19 @@ qxd_status nn_apply_internal(qxd_handle* h, qxd_nn* net, float4* out_e, const fl
 static void wgrad(qxd_handle* h, qxd_nn* net, const uint16_t* gq, const uint16_t* in, int nq, int layer, hipStream_t s) {
   const int cin = kCin[layer], cout = kCout[layer];
   int nchunk = 0, nblk = 0, run = 0;
+  const int len = layer == 1 ? kWgLen : 2 * kWgLen;
   if (net->blk) {
     nblk = (int)NnBlocks(h->geo).count();
     run = wgrad_run(net, nblk);
-    hipLaunchKernelGGL(k_wgrad_blk, dim3(div_up(3 * (int64_t)nblk, run)), dim3(64 * kWgWaves), 0, s, h->geo, nblk, run, gq, in,
-                       net->part);
+    hipLaunchKernelGGL(k_wgrad_blk, dim3(div_up(3 * (int64_t)nblk, run)), dim3(64 * kWgWaves), 0, s, h->geo, nblk, run, len,
+                       gq, in, net->part);
   } else {
     nchunk = div_up(nq, kWgChunk);
     hipLaunchKernelGGL(k_conv_wgrad, dim3(nchunk, div_up(NN_TAPS, 4)), dim3(256), 0, s, h->geo, gq, in, nq, kWgChunk,
                        net->part);
   }
   hipLaunchKernelGGL(k_wgrad_reduce, dim3(div_up(NN_TAPS * cout * cin, 256)), dim3(256), 0, s, net->part, nchunk, nblk,
-                     run, cin,
-                     cout, kOff[layer], net->grad);
+                     run, len, cin, cout, kOff[layer], net->grad);
 }
 
 // loss of one pair (r, e) and, with `backward`, accumulation of its weight
