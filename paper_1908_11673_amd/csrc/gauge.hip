@@ -156,23 +156,20 @@ extern "C" qxd_status qxd_set_gauge(qxd_handle* h, const double* U_phys, const d
     QXD_HIP(hipGetLastError());
     QXD_HIP(hipMemcpyAsync(h->Aphys, A_phys, nA, hipMemcpyDeviceToDevice, s));
   } else {
-    // through a bounded staging buffer
-    const int64_t part = std::min<int64_t>(V, (int64_t)1 << 19);
-    double* stage = nullptr;
-    if (!dev_alloc(&stage, (size_t)part * 18 * sizeof(double))) return QXD_ENOMEM;
-    hipError_t e = hipStreamSynchronize(s);
+    // in parts through the room of the angles, which are copied last: no device
+    // memory beyond what is kept
+    const int64_t part = (int64_t)(nA / (18 * sizeof(double)));  // 2 V / 9 links, V >= 16
+    double* stage = h->Aphys;
+    QXD_HIP(hipStreamSynchronize(s));
     for (int mu = 0; mu < 4; ++mu)
-      for (int64_t s0 = 0; s0 < V && e == hipSuccess; s0 += part) {
+      for (int64_t s0 = 0; s0 < V; s0 += part) {
         const int64_t n = std::min(part, V - s0);
-        e = hipMemcpy(stage, U_phys + (mu * V + s0) * 18, (size_t)n * 18 * sizeof(double), hipMemcpyHostToDevice);
-        if (e != hipSuccess) break;
+        QXD_HIP(hipMemcpy(stage, U_phys + (mu * V + s0) * 18, (size_t)n * 18 * sizeof(double), hipMemcpyHostToDevice));
         hipLaunchKernelGGL(k_gauge_soa, dim3(div_up(n, QXD_BLOCK)), dim3(QXD_BLOCK), 0, s, n, stage,
                            U + mu * 9 * V + s0, V);
-        e = hipGetLastError();
-        if (e == hipSuccess) e = hipStreamSynchronize(s);  // the staging buffer is filled again
+        QXD_HIP(hipGetLastError());
+        QXD_HIP(hipStreamSynchronize(s));  // the next part takes the same room
       }
-    (void)hipFree(stage);
-    QXD_HIP(e);
     QXD_HIP(hipMemcpy(h->Aphys, A_phys, nA, hipMemcpyHostToDevice));
   }
   h->has_gauge = true;
