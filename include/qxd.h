@@ -406,7 +406,7 @@ qxd_status qxd_nn_get_weights(qxd_nn *net, float *w);
 qxd_status qxd_nn_save(qxd_nn *net, const char *path);
 qxd_status qxd_nn_load(qxd_nn *net, const char *path);
 
-/* out_e = |in_e| N(in_e / |in_e|): F32 even half fields. */
+/* out_e = |in_e| N(in_e / |in_e|): F32 even half fields, distinct. */
 qxd_status qxd_nn_apply(qxd_handle *h, qxd_nn *net, void *out_e, const void *in_e, void *stream);
 
 /* Loss and FP32 weight gradient (host, QXD_NN_NWEIGHTS floats) over a batch of
