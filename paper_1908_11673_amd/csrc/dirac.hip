@@ -37,8 +37,9 @@ __device__ __forceinline__ double sp_norm2(const cx<T> s[12]) {
 }
 
 // The outputs of both passes (t_o, chi) are stored either plainly or with the
-// non-temporal hint, chosen at run time (Geo::plain_st, QXD_SCHUR_STORES=plain);
-// every configuration measured is fastest with the non-temporal stores, also in
+// non-temporal hint, chosen at run time (Geo::plain_st, QXD_SCHUR_STORES=plain;
+// the four-wave form below, for lattices that stay in the caches, always stores
+// plainly); every configuration measured is fastest with the non-temporal stores, also in
 // the chunked order where pass 2 reads t_o back soon (FP64 1.70 against
 // 1.73 ms).  With the choice in the kernels the compiler schedules the
 // bf16-storage passes differently: pass 1 issues its last direction's twelve
