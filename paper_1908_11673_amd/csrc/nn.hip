@@ -864,8 +864,8 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(Geo g, const uint16_t* __res
 // (k_conv_wgrad) takes 165 (92 in the last layer, over the even sites only).
 // Four waves of seven taps, one a SIMD, take 54 to 61 us however their LDS
 // reads are scheduled.  One d0 a workgroup, so that a partial sum is 108 kB: 256
-// workgroups of all 81 taps would leave 85 MB; summing the partials takes 7.7 us
-// (33 before, over 128 partials of all taps).
+// workgroups of all 81 taps would leave 85 MB; summing the partials takes 7 to 8 us,
+// 12.5 in layer 2 (33 before, over 128 partials of all taps).
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 
 struct WgLds {
